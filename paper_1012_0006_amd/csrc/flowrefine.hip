@@ -65,6 +65,7 @@ struct DevBufs {
   // per arc
   int32_t *ga = nullptr, *gw = nullptr;
   Arc *arc = nullptr;  // corridor arcs
+  bool arc_small = false;  // no memory for a network row per vertex
   // per block
   int32_t *blk2pair = nullptr;
   int64_t *bstat = nullptr;  // [3k]
@@ -89,6 +90,7 @@ struct fr_context {
   hipStream_t user_stream = nullptr;
   hipStream_t cs = nullptr;  // the library's own stream (graph capture needs a non-null one)
   int num_cus = 0;
+  size_t lds_bytes = 65536;  // LDS a workgroup may take
   // grids of the whole-graph passes: every workgroup resident at once (each
   // wave walks one contiguous run of vertex chunks)
   int g_bnd = 0, g_bstat = 0, g_fstat = 0, g_union = 0;
@@ -171,19 +173,33 @@ static void free_vertex_arc(DevBufs &d) {
 static int32_t ensure_capacity(fr_context *c, int64_t n, int64_t narcs, int64_t k,
                                int64_t slots = 1) {
   DevBufs &d = c->d;
-  const int64_t sn = slots * n, sa = slots * narcs;
-  if (n > d.ncap || narcs > d.acap || sn > d.sncap || sa > d.sacap) {
+  // arc slots: the arcs, or the network rows (fr_rows.h: one per vertex and
+  // at most one more per 16 arcs) where they are more, and the rounding of
+  // each entry's slice to whole cache lines
+  const int64_t sn = slots * n;
+  int64_t sa = slots * std::max(narcs, (int64_t)(ROW_WORDS / 2) * n + narcs / 2 + 1) +
+               8 * FR_MAX_PAIRS;
+  if (n > d.ncap || narcs > d.acap || sn > d.sncap || slots * narcs > d.sacap ||
+      (sa > d.sacap && !d.arc_small)) {
     const int64_t nc = std::max(n, d.ncap), ac = std::max(narcs, d.acap);
-    const int64_t snc = std::max(sn, d.sncap), sac = std::max(sa, d.sacap);
+    const int64_t snc = std::max(sn, d.sncap);
+    int64_t sac = std::max(sa, d.sacap);
     free_vertex_arc(d);
     hipError_t e = hipSuccess;
 #define A_(p, cnt) \
   if (e == hipSuccess) e = dalloc(&d.p, cnt)
     A_(mark, snc); A_(vmap, snc); A_(uvert, snc); A_(lg, snc); A_(lo, snc + FR_MAX_PAIRS + 1);
     A_(ex, snc); A_(lab, snc); A_(ins, snc); A_(LA, snc); A_(LB, snc); A_(SNK, snc);
-    A_(lflag, snc); A_(arc, sac);
+    A_(lflag, snc);
     A_(partw, nc); A_(parts, nc); A_(gx, nc + 1); A_(gv, nc); A_(side, nc);
     A_(ga, ac); A_(gw, ac);
+    A_(arc, sac);
+    if (e == hipErrorOutOfMemory && sac > slots * narcs) {  // the arcs alone: networks in CSR form
+      (void)hipGetLastError();
+      sac = std::max(slots * narcs, (int64_t)1);
+      d.arc_small = true;
+      e = dalloc(&d.arc, sac);
+    }
 #undef A_
     if (e != hipSuccess) {
       free_vertex_arc(d);
@@ -309,6 +325,14 @@ extern "C" int32_t fr_create(int32_t device, void *hip_stream, fr_context **out)
     return FR_E_DEVICE;
   }
   c->num_cus = prop.multiProcessorCount;
+  c->lds_bytes = std::max<size_t>(65536, prop.sharedMemPerBlock);
+  for (const void *fn : {(const void *)k_flow<256>, (const void *)k_flow<512>,
+                         (const void *)k_flow<1024>})
+    if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)c->lds_bytes - 2048) != hipSuccess) {
+      (void)hipGetLastError();
+      c->lds_bytes = 65536;
+    }
   {
     auto resident = [&](const void *fn) {
       int nb = 0;
@@ -329,8 +353,8 @@ extern "C" int32_t fr_create(int32_t device, void *hip_stream, fr_context **out)
 #define A_(p, cnt) \
   if (e == hipSuccess) e = dalloc(&d.p, cnt)
   A_(trace, (int64_t)FR_MAX_PAIRS * FR_MAX_ITERS); A_(ucnt, FR_MAX_PAIRS);
-  A_(qctr, 4 * FR_MAX_ITERS); A_(pcnt, 2 * FR_MAX_PAIRS); A_(pacc, (int64_t)PA_N * FR_MAX_PAIRS);
-  A_(act, FR_MAX_PAIRS); A_(nact, 1); A_(vpre, FR_MAX_PAIRS + 1); A_(cpre, FR_MAX_PAIRS + 1);
+  A_(qctr, FR_QUEUE * FR_MAX_ITERS); A_(pcnt, 3 * FR_MAX_PAIRS); A_(pacc, (int64_t)PA_N * FR_MAX_PAIRS);
+  A_(act, FR_MAX_PAIRS); A_(nact, 2); A_(vpre, FR_MAX_PAIRS + 1); A_(cpre, FR_MAX_PAIRS + 1);
   A_(mpre, FR_MAX_PAIRS + 1);
   A_(srec, FR_MAX_PAIRS);
   A_(voff, FR_MAX_PAIRS + 1); A_(aoff, FR_MAX_PAIRS + 1); A_(fstat, 4 * FR_MAX_PAIRS);
@@ -456,6 +480,14 @@ static iter_fn corr_kernel(int tpb) {
   }
 }
 
+static iter_fn flow_csr_kernel(int tpb) {
+  switch (tpb) {
+    case 256: return k_flow_csr<256>;
+    case 512: return k_flow_csr<512>;
+    default: return k_flow_csr<1024>;
+  }
+}
+
 static iter_fn flow_kernel(int tpb) {
   switch (tpb) {
     case 256: return k_flow<256>;
@@ -573,6 +605,7 @@ static KArgs call_args(fr_context *c, const DevBufs &d, const fr_graph *g, int32
   A.SNK = d.SNK;
   A.lflag = d.lflag;
   A.arc = d.arc;
+  A.arc_cap = d.sacap;
   A.ctl = d.ctl;
   A.tpv = c->tune.tpv;
   A.relabel_period = c->tune.relabel_period;
@@ -655,7 +688,7 @@ static int32_t call_constants(fr_context *c, KArgs &A, int64_t narcs, const fr_p
     int32_t rc = validate_graph(c, A, narcs, may_alloc);
     if (rc) return rc;
   }
-  hipLaunchKernelGGL(k_graph_stats, dim3(sblocks), dim3(256), 0, st, A);
+  hipLaunchKernelGGL(k_graph_stats, dim3(sblocks), dim3(256), 0, st, A, narcs);
   HIPCHK(hipGetLastError());
   HIPCHK(hipMemcpyAsync(c->h_ctl, d.ctl, sizeof(Ctl), hipMemcpyDeviceToHost, st));
   HIPCHK(hipStreamSynchronize(st));
@@ -697,6 +730,34 @@ static int blocks_of(const fr_context *c, int32_t P) {
   return (int)std::max<int64_t>(1, std::min<int64_t>(P, slots));
 }
 
+static size_t solve_shared_bytes(int tpb) {
+  return tpb == 256   ? sizeof(SolveShared<256>)
+         : tpb == 512 ? sizeof(SolveShared<512>)
+                      : sizeof(SolveShared<1024>);
+}
+
+// Dynamic LDS of the flow kernel, for workgroups of tpb threads, and what of
+// it the row networks may use: a CU's whole LDS shared by the workgroups that
+// the launch puts on one (labels of corridors up to about 60,000 vertices
+// then fit beside the bitmaps with one workgroup per CU, about 27,000 with
+// two).
+static size_t flow_lds_bytes(const fr_context *c, int32_t blocks, int tpb) {
+  const size_t fixed = solve_shared_bytes(tpb);
+  const size_t per_cu = (size_t)std::max(1, (blocks + c->num_cus - 1) / c->num_cus);
+  const size_t share = (c->lds_bytes / per_cu) & ~(size_t)2047;
+  const size_t other = 2048;  // the kernel's other shared variables
+  return std::max(fixed, share > other ? share - other : 0);
+}
+
+static void set_row_limits(KArgs &A, size_t bytes, int tpb) {
+  const size_t off = tpb == 256   ? offsetof(SolveShared<256>, u)
+                     : tpb == 512 ? offsetof(SolveShared<512>, u)
+                                  : offsetof(SolveShared<1024>, u);
+  A.flow_lds = (int64_t)(bytes - off);
+  // largest multiple of 64 with row_lds_bytes(nr) <= flow_lds
+  A.row_nr = (A.flow_lds - row_lds_bytes(0)) / 16 * 64;
+}
+
 // All kernels of one matching round: setup kernels, then the launches of
 // the per-iteration chain (pairs that stopped are skipped inside).  With
 // captured set, device-only work (max_iters launches, no host read-back),
@@ -708,6 +769,19 @@ static int32_t enqueue_round(fr_context *c, KArgs A, bool use_mlp, hipStream_t s
                              bool captured) {
   DevBufs &d = c->d;
   const int sblocks = std::min(4 * c->num_cus, 8192);
+  const int tpb = c->tune.block_threads;
+  const int blocks = blocks_of(c, A.P);
+  const bool fused = c->fused && A.mb_reps == 0 && A.W == 1;
+  const size_t flow_lds = flow_lds_bytes(c, blocks, tpb);
+  set_row_limits(A, flow_lds, tpb);
+  if (fused) A.row_nr = -1;  // k_round builds and solves the CSR form
+  // no network of the round can need the CSR form (every vertex and arc fits
+  // a row, and so do all rows the array): its kernels stay away
+  const bool all_rows =
+      !fused && c->h_ctl->maxdeg <= ROW_MAX_DEG && c->h_ctl->maxw <= ROW_MAX_W &&
+      A.n <= A.row_nr &&
+      A.W * (ROW_WORDS / 2 * (int64_t)A.n + A.narcs / 2) + 8 * (int64_t)A.P <= A.arc_cap;
+  A.all_rows = all_rows ? 1 : 0;
   A.fstat = use_mlp ? d.fstat : nullptr;
   hipLaunchKernelGGL(k_round_init, dim3(1), dim3(1024), 0, st, A);
   hipLaunchKernelGGL(k_block_stats, dim3(c->g_bstat), dim3(256), 0, st, A);
@@ -730,10 +804,8 @@ static int32_t enqueue_round(fr_context *c, KArgs A, bool use_mlp, hipStream_t s
     hipLaunchKernelGGL(k_fm_gain, dim3(sblocks), dim3(256), 0, st, A);
     hipLaunchKernelGGL(k_fm, dim3(A.P / A.W), dim3(FM_TPB), 0, st, A);
   }
-  const int tpb = c->tune.block_threads;
-  const int blocks = blocks_of(c, A.P);
-  const iter_fn corr = corr_kernel(tpb), flow = flow_kernel(tpb);
-  const bool fused = c->fused && A.mb_reps == 0 && A.W == 1;
+  const iter_fn corr = corr_kernel(tpb), flow = flow_kernel(tpb),
+                flow_csr = flow_csr_kernel(tpb);
   // sliced rounds need the host between launches (how many follow is read
   // back), so a captured round passes slice_ticks = 0; a round of one pair
   // has no other pair to wait for
@@ -789,11 +861,14 @@ static int32_t enqueue_round(fr_context *c, KArgs A, bool use_mlp, hipStream_t s
     hipLaunchKernelGGL(k_iter_mid, dim3(1), dim3(1024), 0, st, A, it);
     if (timed) HIPCHK(hipEventRecord(ev[1], st));
     hipLaunchKernelGGL(k_net_count, dim3(sblocks), dim3(256), 0, st, A, it);
-    hipLaunchKernelGGL(k_net_scan, dim3(A.P), dim3(1024), 0, st, A, it);
-    hipLaunchKernelGGL(k_net_fill, dim3(sblocks), dim3(256), 0, st, A, it);
+    if (!all_rows) {
+      hipLaunchKernelGGL(k_net_scan, dim3(A.P), dim3(1024), 0, st, A, it);
+      hipLaunchKernelGGL(k_net_fill, dim3(sblocks), dim3(256), 0, st, A, it);
+    }
     hipLaunchKernelGGL(k_net_rev, dim3(sblocks), dim3(256), 0, st, A, it);
     if (timed) HIPCHK(hipEventRecord(ev[2], st));
-    hipLaunchKernelGGL(flow, dim3(blocks), dim3(tpb), 0, st, A, it);
+    hipLaunchKernelGGL(flow, dim3(blocks), dim3(tpb), flow_lds, st, A, it);
+    if (!all_rows) hipLaunchKernelGGL(flow_csr, dim3(blocks), dim3(tpb), 0, st, A, it);
     if (timed) HIPCHK(hipEventRecord(ev[3], st));
     if (A.mb_reps > 0) {
       hipLaunchKernelGGL(k_mb_scan, dim3(1), dim3(1024), 0, st, A, it);
@@ -1116,6 +1191,7 @@ static int32_t refine(fr_context *c, const fr_graph *g, int32_t *part, int32_t k
   (void)hipEventRecord(c->ev[0], st);
   HIPCHK(hipMemcpyAsync(d.partw, s.dpart, sizeof(int32_t) * n, hipMemcpyDeviceToDevice, st));
   KArgs A = call_args(c, d, &s.g, d.partw, k, p);
+  A.narcs = s.narcs;
   A.W = W;
   A.mstride = W > 1 ? n : 0;
   if ((rc = call_constants(c, A, s.narcs, p, carve == nullptr))) return rc;
@@ -1241,6 +1317,7 @@ extern "C" int32_t flow_refine_pair_static(fr_context *c, const fr_graph *g, int
   take(&v.partw, vn);
   take(&v.lflag, (size_t)n);
   take(&v.arc, sizeof(Arc) * (size_t)narcs);
+  v.sacap = narcs;
   take(&v.blk2pair, sizeof(int32_t) * 3 * (size_t)k);
   take(&v.bstat, sizeof(int64_t) * 3 * (size_t)k);
   if (!fits) return FR_E_SCRATCH_LIMIT;
@@ -1347,6 +1424,7 @@ extern "C" int32_t flow_refine_sweep(fr_context *c, const fr_graph *g, int32_t *
   reset_stats(c);
   (void)hipEventRecord(c->ev[0], st);
   KArgs A = call_args(c, d, &s.g, work, k, p);
+  A.narcs = s.narcs;
   A.mstride = g->n;
   if ((rc = call_constants(c, A, s.narcs, p))) return rc;
   int64_t acc[4] = {0, 0, 0, 0};

@@ -6,6 +6,7 @@
 
 #define FR_MAX_ALPHA 1024
 #define FR_MAX_ITERS 64
+#define FR_QUEUE 8  // queue words per launch
 
 // A corridor arc: local head, index of its reverse arc, and the residual
 // pair -- the arc's own residual capacity in the low 32 bits, the reverse
@@ -53,6 +54,7 @@ struct PairState {
   int32_t phase, iter;
   int64_t solve_sweeps;
   int32_t rp_eff, slices;
+  int32_t rows, pad;  // the entry's current network is in the row form (fr_rows.h)
 };
 
 // work counters: the data each phase of a solve touches
@@ -83,6 +85,7 @@ enum {
   PA_RCAP,     // their capacity sum
   PA_RCIN,     // weight of the old a-b edges the solve decides
   PA_CS,       // contracted terminals: capacity out of s (the initial excess)
+  PA_MISFIT,   // corridor vertices that do not fit the row form
   PA_N
 };
 
@@ -95,6 +98,7 @@ struct Ctl {
   int32_t live;         // entries still iterating (sliced rounds, read by the host)
   int64_t cV;           // total vertex weight
   int64_t maxc;         // max vertex weight
+  int32_t maxdeg, maxw; // largest degree and edge weight
 };
 
 enum { DIAG_NONE = 0, DIAG_LIST = 1, DIAG_CLOSURE = 2, DIAG_REV = 3, DIAG_SWEEPS = 4,
@@ -103,6 +107,7 @@ enum { DIAG_NONE = 0, DIAG_LIST = 1, DIAG_CLOSURE = 2, DIAG_REV = 3, DIAG_SWEEPS
 struct KArgs {
   // graph (device)
   int32_t n, k;
+  int64_t narcs;
   const int32_t *xadj, *adjncy, *adjwgt, *vwgt;
   int32_t *part;
   // pairs of this round (one matching)
@@ -116,9 +121,10 @@ struct KArgs {
   PairState *ps;            // [P]
   fr_solve *trace;          // [P * max_iters] or null
   int64_t *bstat;           // [3k] weight, vertex count, arc count per block
-  int32_t *queue;           // [2 * max_iters] pair-queue counters: corridor and flow kernels
+  int32_t *queue;           // [FR_QUEUE * max_iters] counters of a launch: corridor queue, then
+                            // queue, running and started entries of k_flow and of k_flow_csr
   int64_t *pacc;            // [P * PA_N] per-pair sums of the current solve
-  int32_t *pcnt;            // [2P] boundary-list and sink-list counters
+  int32_t *pcnt;            // [3P] boundary-list, sink-list and overflow-row counters
   // Speculative slots: every pair of the round owns W consecutive entries
   // (pair p, slot s at index p * W + s) that solve the same partition at the
   // factors alpha, alpha/2, ... of its halving chain at once; each slot has
@@ -129,7 +135,7 @@ struct KArgs {
   fr_solve *srec;           // [P] record of each entry's solve in the current launch
   // pairs still iterating in the current launch, compacted: act[0..nact),
   // prefix sums of their union sizes (vpre) and corridor sizes (cpre)
-  int32_t *act, *nact;
+  int32_t *act, *nact;      // nact[1]: how many of them took the CSR network form
   int64_t *vpre, *cpre;
   int64_t *fstat;           // [4P] boundary statistics for the learned factor
   const int64_t *base;      // floor((1 + alpha eps) c(V) / k), alpha = 0..alpha_max
@@ -180,7 +186,9 @@ struct KArgs {
   int32_t *lo;              // local CSR offsets (n + P slots: nv_p + 1 per pair)
   int32_t *ex, *lab, *ins, *LA, *LB, *SNK;
   uint8_t *lflag;
-  Arc *arc;                 // local arcs (one 16-byte record each)
+  Arc *arc;                 // local arcs: rows (fr_rows.h) or one 16-byte record each
+  int64_t arc_cap;          // its length in records
+  int32_t all_rows;         // no network of the round needs the CSR form
   Ctl *ctl;
   // launch
   int32_t tpv, relabel_period;
@@ -188,6 +196,9 @@ struct KArgs {
   // before it stops at the next due global relabel (0: run to the end)
   int64_t slice_ticks;
   int64_t max_sweeps;
+  // row networks: bytes of the flow kernel's LDS they may use, and the
+  // largest corridor whose bitmaps and lists fit them
+  int64_t flow_lds, row_nr;
   int8_t *side_out;
 };
 

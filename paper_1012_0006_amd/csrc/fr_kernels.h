@@ -39,6 +39,12 @@ __device__ __forceinline__ int lane64() { return (int)__lane_id(); }
 // stay scalar.
 __device__ __forceinline__ int32_t uni(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }
 
+__device__ __forceinline__ int64_t uni64(int64_t v) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)(uint32_t)v);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)(uint32_t)(v >> 32));
+  return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+
 // Append for lanes with want=true among the ACTIVE lanes of the wave: one
 // atomic per wave on *counter (LDS or global).  Returns the slot or -1.
 __device__ __forceinline__ int wave_append(int32_t *counter, bool want) {
@@ -119,6 +125,16 @@ __device__ void block_sums(int64_t (&v)[N], int64_t *lds) {
   for (int64_t _b = (int64_t)(threadIdx.x & ~63u); _b < (int64_t)(N); _b += blockDim.x) \
     for (int64_t i = _b + lane64(), _once = 1; _once; _once = 0)
 
+// LDS working set of the flow phases: two vertex bitmaps (visited marks of
+// the relabel and closure searches, queued marks of the sweeps) cover
+// corridors of up to 32 * FR_BM_WORDS vertices; larger corridors use the
+// global label / mark arrays instead.  The first FR_LDS_LIST entries of each
+// frontier list live in LDS, the rest in the pair's global list.
+#define FR_BM_WORDS 4096
+#define FR_LDS_LIST 2048
+
+#include "fr_rows.h"
+
 // ------------------------------------------------------------------------
 // setup kernels
 
@@ -168,23 +184,28 @@ struct KeyedSums {
   int key = -1;
   int64_t v[N];
   __device__ KeyedSums() {
+#pragma unroll
     for (int j = 0; j < N; j++) v[j] = 0;
   }
   template <typename Out>
   __device__ __forceinline__ void add(int k, const int64_t (&x)[N], Out &&out) {
     const bool change = key >= 0 && k >= 0 && k != key;
     if (__ballot(change)) {
+#pragma unroll
       for (int j = 0; j < N; j++) out(j, change ? key : -1, v[j]);
       if (change)
+#pragma unroll
         for (int j = 0; j < N; j++) v[j] = 0;
     }
     if (k >= 0) {
       key = k;
+#pragma unroll
       for (int j = 0; j < N; j++) v[j] += x[j];
     }
   }
   template <typename Out>
   __device__ __forceinline__ void flush(Out &&out) {
+#pragma unroll
     for (int j = 0; j < N; j++) out(j, key, v[j]);
   }
 };
@@ -273,18 +294,23 @@ __device__ __forceinline__ void chunk_boundary(const KArgs &A, int32_t x0, int32
   cw = (int64_t)scw[lane];
 }
 
-// c(V), max c(v) and the range check of the partition (once per call).
-__global__ void __launch_bounds__(256) k_graph_stats(KArgs A) {
+// c(V), max c(v), the range check of the partition, and the largest degree
+// and edge weight (which networks may need the CSR form); once per call.
+__global__ void __launch_bounds__(256) k_graph_stats(KArgs A, int64_t narcs) {
   __shared__ int64_t s_red[16];
   int64_t sum = 0;
-  int32_t mx = 0;
+  int32_t mx = 0, md = 0, mw = 0;
   int bad = 0;
+  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < narcs;
+       e += (int64_t)gridDim.x * blockDim.x)
+    mw = max(mw, A.adjwgt[e]);
   for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u < A.n;
        u += (int64_t)gridDim.x * blockDim.x) {
     const int32_t w = A.vwgt[u];
     const int32_t x = A.part[u];
     sum += w;
     mx = w > mx ? w : mx;
+    md = max(md, A.xadj[u + 1] - A.xadj[u]);
     if (w < 0) bad |= 2;
     if (x < 0 || x >= A.k) bad |= 1;
   }
@@ -292,10 +318,13 @@ __global__ void __launch_bounds__(256) k_graph_stats(KArgs A) {
   block_sums<1>(v, s_red);
   if (threadIdx.x == 0) atomicAdd((unsigned long long *)&A.ctl->cV, (unsigned long long)v[0]);
   for (int o = 32; o > 0; o >>= 1) {
-    const int32_t t = __shfl_xor(mx, o);
-    mx = t > mx ? t : mx;
+    mx = max(mx, __shfl_xor(mx, o));
+    md = max(md, __shfl_xor(md, o));
+    mw = max(mw, __shfl_xor(mw, o));
   }
   if (lane64() == 0 && mx > 0) atomicMax((long long *)&A.ctl->maxc, (long long)mx);
+  if (lane64() == 0 && md > 0) atomicMax(&A.ctl->maxdeg, md);
+  if (lane64() == 0 && mw > 0) atomicMax(&A.ctl->maxw, mw);
   if (bad & 1) atomicOr(&A.ctl->bad_part, 1);
   if (bad & 2) atomicOr(&A.ctl->bad_graph, 1);
 }
@@ -312,9 +341,9 @@ __global__ void __launch_bounds__(1024) k_round_init(KArgs A) {
   for (int i = threadIdx.x; i < A.P; i += blockDim.x) A.ucnt[i] = 0;
   if (A.fstat)
     for (int i = threadIdx.x; i < 4 * A.P; i += blockDim.x) A.fstat[i] = 0;
-  for (int i = threadIdx.x; i < 4 * A.max_iters; i += blockDim.x) A.queue[i] = 0;
+  for (int i = threadIdx.x; i < FR_QUEUE * A.max_iters; i += blockDim.x) A.queue[i] = 0;
   for (int i = threadIdx.x; i < A.P * PA_N; i += blockDim.x) A.pacc[i] = 0;
-  for (int i = threadIdx.x; i < 2 * A.P; i += blockDim.x) A.pcnt[i] = 0;
+  for (int i = threadIdx.x; i < 3 * A.P; i += blockDim.x) A.pcnt[i] = 0;
   __syncthreads();
   for (int i = threadIdx.x; i < A.P; i += blockDim.x) {
     if (i % A.W) continue;  // a pair's blocks map to its first entry
@@ -356,18 +385,33 @@ __global__ void __launch_bounds__(1024) k_arena(KArgs A) {
   const int per = (P + blockDim.x - 1) / blockDim.x;
   const int lo = threadIdx.x * per, hi = min(lo + per, P);
   int64_t sv = 0, sa = 0;
-  for (int i = lo; i < hi; i++) {
-    sv += bc[A.pairs[2 * i]] + bc[A.pairs[2 * i + 1]];
-    sa += ba[A.pairs[2 * i]] + ba[A.pairs[2 * i + 1]];
-  }
+  for (int i = lo; i < hi; i++) sv += bc[A.pairs[2 * i]] + bc[A.pairs[2 * i + 1]];
   int64_t tv, ta;
   int64_t rv = block_exscan64(sv, &tv, s_scan);
-  int64_t ra = block_exscan64(sa, &ta, s_scan);
+  // arc slices, in whole cache lines: the rows alone when the call has no
+  // other form; else both forms as far as the array has the room, or the arc
+  // records alone (last without the rounding).  A vertex of d arcs needs its
+  // row and at most d / 16 overflow rows.
+  auto slice = [&](int i, int how) {
+    const int32_t a = A.pairs[2 * i], b = A.pairs[2 * i + 1];
+    const int64_t na = ba[a] + ba[b];
+    const int64_t rows = ROW_WORDS / 2 * (bc[a] + bc[b]) + na / 2;
+    const int64_t x = A.all_rows ? rows : (how == 0 ? max(na, rows) : na);
+    return how < 2 ? (x + 7) & ~7ll : x;
+  };
+  int how = 0;
+  int64_t ra;
+  for (;; how++) {
+    sa = 0;
+    for (int i = lo; i < hi; i++) sa += slice(i, how);
+    ra = block_exscan64(sa, &ta, s_scan);
+    if (ta <= A.arc_cap || how == 2) break;
+  }
   for (int i = lo; i < hi; i++) {
     A.voff[i] = rv;
     A.aoff[i] = ra;
     rv += bc[A.pairs[2 * i]] + bc[A.pairs[2 * i + 1]];
-    ra += ba[A.pairs[2 * i]] + ba[A.pairs[2 * i + 1]];
+    ra += slice(i, how);
   }
   if (threadIdx.x == 0) {
     A.voff[P] = tv;
@@ -545,23 +589,8 @@ __global__ void __launch_bounds__(256) k_union(KArgs A) {
 // per-pair solver
 
 // Shared-memory state of one workgroup.
-// LDS working set of the flow phases: two vertex bitmaps (visited marks of
-// the relabel and closure searches, queued marks of the sweeps) cover
-// corridors of up to 32 * FR_BM_WORDS vertices; larger corridors use the
-// global label / mark arrays instead.  The first FR_LDS_LIST entries of each
-// frontier list live in LDS, the rest in the pair's global list.
-#define FR_BM_WORDS 4096
-#define FR_LDS_LIST 2048
-
 template <int TPB>
 struct SolveShared {
-  union {
-    unsigned long long hist[2048];  // radix select of the last BFS level
-    struct {
-      uint32_t bm[2][FR_BM_WORDS];
-      int32_t ls[2][FR_LDS_LIST];
-    } f;
-  } u;
   int64_t red[16 * 8];            // block reductions
   int64_t scan[TPB / 64 + 1];
   int64_t W[2], U[2];             // BFS: taken weight and bound per side
@@ -580,6 +609,14 @@ struct SolveShared {
   int32_t digit;
   int32_t stop;
   int64_t before;
+  // last: the flow kernel's launch may extend it (row solver)
+  union {
+    unsigned long long hist[2048];  // radix select of the last BFS level
+    struct {
+      uint32_t bm[2][FR_BM_WORDS];
+      int32_t ls[2][FR_LDS_LIST];
+    } f;
+  } u;
 };
 
 // The last level of one side (block x) is cut in ascending id: find the first
@@ -1111,14 +1148,16 @@ __device__ __forceinline__ int32_t pair_of(const int64_t *voff, int32_t P, int64
   return lo;
 }
 
+// (p is the same in every lane: scalar registers, so that the solver's loops
+// keep their vector registers for the work)
 __device__ __forceinline__ PairView make_view(const KArgs &A, int32_t p) {
   PairView V;
-  V.a = A.pairs[2 * p];
-  V.b = A.pairs[2 * p + 1];
-  const int64_t vb = A.voff[p];
-  const int64_t ab = A.aoff[p];
-  V.nv = A.voff[p + 1] - vb;
-  V.na = A.aoff[p + 1] - ab;
+  V.a = uni(A.pairs[2 * p]);
+  V.b = uni(A.pairs[2 * p + 1]);
+  const int64_t vb = uni64(A.voff[p]);
+  const int64_t ab = uni64(A.aoff[p]);
+  V.nv = uni64(A.voff[p + 1]) - vb;
+  V.na = uni64(A.aoff[p + 1]) - ab;
   V.uv = A.uvert + vb;
   V.lg = A.lg + vb;
   V.lo = A.lo + vb + p;
@@ -1153,7 +1192,7 @@ __device__ __forceinline__ int32_t *vmap_of(const KArgs &A, int32_t p) {
 // trip count is uniform over each wave.
 template <typename F>
 __device__ __forceinline__ void grid_items(const KArgs &A, const int64_t *pre, F &&f) {
-  const int32_t na = *A.nact;
+  const int32_t na = A.nact[0];
   const int64_t N = pre[na];
   for (int64_t b0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) & ~(int64_t)63; b0 < N;
        b0 += (int64_t)gridDim.x * blockDim.x) {
@@ -1175,9 +1214,8 @@ __device__ __forceinline__ void grid_items(const KArgs &A, const int64_t *pre, F
 __global__ void __launch_bounds__(1024) k_iter_begin(KArgs A, int32_t it) {
   __shared__ int64_t s_scan[17];
   const int P = A.P;
-  // this launch's counters (a ring over max_iters launches): the corridor
-  // and flow queues, the flow's running and started entries
-  if (threadIdx.x < 4) A.queue[4 * (it % A.max_iters) + threadIdx.x] = 0;
+  // this launch's counters (a ring over max_iters launches)
+  if (threadIdx.x < FR_QUEUE) A.queue[FR_QUEUE * (it % A.max_iters) + threadIdx.x] = 0;
   const int per = (P + blockDim.x - 1) / blockDim.x;
   const int lo = threadIdx.x * per, hi = min(lo + per, P);
   // the entries whose next corridor is due (the others are idle, or in a
@@ -1200,7 +1238,8 @@ __global__ void __launch_bounds__(1024) k_iter_begin(KArgs A, int32_t it) {
       rs += A.voff[i + 1] - A.voff[i];
     }
   if (threadIdx.x == 0) {
-    *A.nact = (int32_t)tc;
+    A.nact[0] = (int32_t)tc;
+    A.nact[1] = 0;  // entries of this launch in the CSR form
     A.vpre[tc] = ts;
   }
   // per block of the round: its pair's first entry while a slot's corridor
@@ -1530,7 +1569,7 @@ __global__ void __launch_bounds__(TPB) k_corr(KArgs A, int32_t it) {
   __shared__ SolveShared<TPB> sh;
   __shared__ PairState st;
   for (;;) {
-    const int32_t p = next_pair<TPB>(A, A.queue + 4 * (it % A.max_iters), sh, 0);
+    const int32_t p = next_pair<TPB>(A, A.queue + FR_QUEUE * (it % A.max_iters), sh, 0);
     if (p < 0) break;
     corr_pair<TPB>(A, stamp_of(A, p), p, sh, st);
   }
@@ -1543,17 +1582,21 @@ __global__ void __launch_bounds__(TPB) k_corr(KArgs A, int32_t it) {
 //      outside the corridor is the capacity of s -> u (written as u's initial
 //      excess), the weight into b outside that of u -> t (written to SNK),
 //      and the old a-b edges with one end outside count as decided too.
+//      The arcs go straight into the vertex's row (fr_rows.h) as they are
+//      found; a vertex that does not fit the row form counts as a misfit, and
+//      an entry with misfits takes the CSR form (passes 2 and 3).
 template <typename Items>
 __device__ __forceinline__ void net_count(const KArgs &A, Items &&items) {
   const bool term = A.terminals != 0;
   unsigned long long *acc = (unsigned long long *)A.pacc;
   unsigned long long *psw = (unsigned long long *)A.ps;
   // corridor arcs, capacity sum, decided old a-b weight, vertices, arcs
-  // scanned, capacity out of s
-  KeyedSums<6> sums;
+  // scanned, capacity out of s, misfits
+  KeyedSums<7> sums;
   auto out = [&](int j, int key, int64_t v) {
     if (j < 3) wave_add_by_key(acc, PA_N, PA_RARCS + j, key, v);
     else if (j == 5) wave_add_by_key(acc, PA_N, PA_CS, key, v);
+    else if (j == 6) wave_add_by_key(acc, PA_N, PA_MISFIT, key, v);
     else wave_add_by_key(psw, PS_WORDS, PS_WORK + (j == 3 ? W_NET_VERTS : W_NET_ARCS), key, v);
   };
   items([&](int32_t p, int64_t item) {
@@ -1563,23 +1606,54 @@ __device__ __forceinline__ void net_count(const KArgs &A, Items &&items) {
     const int32_t u = on ? A.lg[i] : 0;
     const int side = on && A.part[u] == b;
     const int32_t *mk = on ? mark_of(A, p) : A.mark;
+    const int32_t *vm = on ? vmap_of(A, p) : A.vmap;
     const int32_t S = on ? stamp_of(A, p) : 0;
     const int32_t e0 = on ? A.xadj[u] : 0, e1 = on ? A.xadj[u + 1] : 0;
+    // the vertex's row and overflow rows (as many as its degree may need,
+    // taken from the entry's counter); fit: they lie in the arc slice
+    const int64_t nr = on ? A.ps[p].nr : 0;
+    bool fit = on && rows_possible(A, p) && e1 - e0 <= ROW_MAX_DEG;
+    u64 *L = on ? rows_of(A, p) : nullptr;
+    const int32_t want = fit ? row_overflow(e1 - e0) : 0;
+    const int32_t ovf = rows_take(A.pcnt + 2 * A.P, p, want);
+    if (fit && want > 0 && ROW_WORDS / 2 * (nr + ovf + want) > A.aoff[p + 1] - A.aoff[p])
+      fit = false;
+    u64 *own = fit ? L + ROW_WORDS * item + 1 : nullptr;
+    u64 *more = fit ? L + ROW_WORDS * (nr + ovf) - ROW_SLOTS : nullptr;
     int64_t cnt = 0, cap = 0, cin = 0, cs = 0, ct = 0;
     bool border = false;
-    for (int32_t e = e0; e < e1; e++) {
-      const int32_t v = A.adjncy[e];
-      const int32_t xv = A.part[v];
-      if (xv != a && xv != b) continue;
-      if (mk[v] == S) {
-        cnt++;
-        cap += A.adjwgt[e];
-        if (!side && xv == b) cin += A.adjwgt[e];
-      } else {
-        border = true;
-        if (xv == a) cs += A.adjwgt[e];
-        else ct += A.adjwgt[e];
-        if (term && xv != (side ? b : a)) cin += A.adjwgt[e];
+    // four arcs per step, their loads issued together
+    for (int32_t c = e0; c < e1; c += 4) {
+      int32_t v[4], w[4], xv[4], mv[4], lv[4];
+#pragma unroll
+      for (int q = 0; q < 4; q++) {
+        const bool in = c + q < e1;
+        v[q] = in ? A.adjncy[c + q] : 0;
+        w[q] = in ? A.adjwgt[c + q] : 0;
+      }
+#pragma unroll
+      for (int q = 0; q < 4; q++) {
+        const bool in = c + q < e1;
+        xv[q] = in ? A.part[v[q]] : -1;
+        mv[q] = in ? mk[v[q]] : S - 1;
+        lv[q] = in ? vm[v[q]] : 0;
+      }
+#pragma unroll
+      for (int q = 0; q < 4; q++) {
+        if (xv[q] != a && xv[q] != b) continue;
+        if (c + q >= e1) continue;
+        if (mv[q] == S) {
+          if (w[q] > ROW_MAX_W) fit = false;
+          if (fit) (cnt < ROW_SLOTS ? own : more)[cnt] = row_word(w[q], w[q], lv[q], 0);
+          cnt++;
+          cap += w[q];
+          if (!side && xv[q] == b) cin += w[q];
+        } else {
+          border = true;
+          if (xv[q] == a) cs += w[q];
+          else ct += w[q];
+          if (term && xv[q] != (side ? b : a)) cin += w[q];
+        }
       }
     }
     border = border && !term;
@@ -1587,14 +1661,21 @@ __device__ __forceinline__ void net_count(const KArgs &A, Items &&items) {
     else cs = 0;
     const bool lead = on;
     if (lead) {
+      if (fit) {  // header, unused words
+        own[-1] = ((u64)(uint32_t)cnt << 32) | (u64)(uint32_t)ovf;
+        for (int32_t q = (int32_t)cnt; q < ROW_SLOTS + ROW_WORDS * want; q++)
+          (q < ROW_SLOTS ? own : more)[q] = 0ull;
+      }
       A.lo[i + p + 1] = (int32_t)cnt;  // the pair's offsets start at voff[p] + p
       A.lflag[i] = (uint8_t)((side ? LF_SIDE_B : 0u) | (border ? LF_BORDER : 0u));
       if (term) {  // clamped: past 2^31 the pair reports FR_E_OVERFLOW before any use
         A.ex[i] = (int32_t)min<int64_t>(cs, 0x7fffffffLL);
         A.SNK[i] = (int32_t)min<int64_t>(ct, 0x7fffffffLL);
+      } else {
+        A.ex[i] = 0;
       }
     }
-    const int64_t x[6] = {cnt, cap, cin, 1, e1 - e0, cs};
+    const int64_t x[7] = {cnt, cap, cin, 1, e1 - e0, cs, fit ? 0 : 1};
     sums.add(lead ? p : -1, x, out);
   });
   sums.flush(out);
@@ -1605,8 +1686,8 @@ __global__ void __launch_bounds__(256) k_net_count(KArgs A, int32_t it) {
   net_count(A, [&](auto &&f) { grid_items(A, A.cpre, f); });
 }
 
-// pass 2 (one block per pair): inclusive scan of the arc counts into CSR
-// offsets, 4 values per thread per tile
+// pass 2 (one block per pair, CSR form only): inclusive scan of the arc
+// counts into CSR offsets, 4 values per thread per tile
 // s_scan: blockDim.x / 64 + 1 LDS words.  All threads call it.
 __device__ __forceinline__ void net_scan_pair(const KArgs &A, int32_t p, int64_t *s_scan) {
   const int32_t nr = uni(A.ps[p].nr);
@@ -1633,7 +1714,6 @@ __device__ __forceinline__ void net_scan_pair(const KArgs &A, int32_t p, int64_t
   }
   if (threadIdx.x == 0) {
     lo[0] = 0;
-    A.ps[p].last_nr = nr;
   }
 }
 
@@ -1642,14 +1722,17 @@ __global__ void __launch_bounds__(1024) k_net_scan(KArgs A, int32_t it) {
   (void)it;
   const int32_t p = blockIdx.x;
   if (p >= A.P || A.ps[p].done || A.ps[p].phase != 0) return;
+  if (rows_chosen(A, p)) return;
+  if (threadIdx.x == 0) atomicAdd(A.nact + 1, 1);
   net_scan_pair(A, p, s_scan);
 }
 
-// pass 3: arcs (local head and capacity) in the order of the global adjacency
+// pass 3 (CSR form only): arcs (local head and capacity) in the order of the
+// global adjacency
 template <typename Items>
 __device__ __forceinline__ void net_fill(const KArgs &A, Items &&items) {
   items([&](int32_t p, int64_t item) {
-    if (p < 0) return;
+    if (p < 0 || rows_chosen(A, p)) return;
     const int32_t S = stamp_of(A, p);
     const int64_t i = A.voff[p] + item;  // arena slot
     const int32_t a = A.pairs[2 * p], b = A.pairs[2 * p + 1];
@@ -1692,11 +1775,70 @@ __device__ __forceinline__ void net_fill(const KArgs &A, Items &&items) {
 
 __global__ void __launch_bounds__(256) k_net_fill(KArgs A, int32_t it) {
   (void)it;
+  if (A.nact[1] == 0) return;  // every entry of this launch took the row form
   net_fill(A, [&](auto &&f) { grid_items(A, A.cpre, f); });
 }
 
 // pass 4: reverse arcs, the initial preflow (every arc out of the source
-// border is saturated), cleared closure marks, the sink list
+// border is saturated), the sink list
+//
+// Row form: the lower end of each edge finds the arc's slot in the other row
+// and finishes both words (reverse slots, and the saturation when one end is
+// a source-border vertex; the excess then goes to the other end).
+__device__ __forceinline__ void net_rev_row(const KArgs &A, int32_t p, int32_t i, bool src,
+                                            bool saturate) {
+  u64 *L = rows_of(A, p);
+  const int32_t nr = A.ps[p].nr;
+  const int64_t vb = A.voff[p];
+  const uint8_t *fl = A.lflag + vb;
+  const u64 head = L[(int64_t)ROW_WORDS * i];
+  const int32_t deg = (int32_t)(head >> 32), ovf = (int32_t)(uint32_t)head;
+  for (int32_t s = 0; s < deg; s++) {
+    const int64_t at = s < ROW_SLOTS ? (int64_t)ROW_WORDS * i + 1 + s
+                                     : (int64_t)ROW_WORDS * (nr + ovf) + (s - ROW_SLOTS);
+    const u64 x = L[at];
+    const int32_t h = row_head(x);
+    if (h < i) continue;
+    // its slot in h's row: the own row first, eight 16-byte loads together
+    const u64x2 *R = reinterpret_cast<const u64x2 *>(L + (int64_t)ROW_WORDS * h);
+    u64 y[ROW_WORDS];
+#pragma unroll
+    for (int q = 0; q < ROW_WORDS / 2; q++) {
+      const u64x2 v = R[q];
+      y[2 * q] = v.x;
+      y[2 * q + 1] = v.y;
+    }
+    const int32_t dh = (int32_t)(y[0] >> 32);
+    int32_t t = -1;
+#pragma unroll
+    for (int q = 1; q < ROW_WORDS; q++)
+      if (q <= dh && row_head(y[q]) == i) t = q - 1;
+    if (t < 0) {
+      const u64 *more = L + (int64_t)ROW_WORDS * (nr + (int32_t)(uint32_t)y[0]) - ROW_SLOTS;
+      for (int32_t q = ROW_SLOTS; q < dh; q++)
+        if (row_head(more[q]) == i) {
+          t = q;
+          break;
+        }
+    }
+    if (t < 0) {  // asymmetric input slipped past validation
+      A.ctl->err = FR_E_INVALID_GRAPH;
+      A.ctl->diag = DIAG_REV;
+      continue;
+    }
+    const int32_t c = row_own(x);
+    const bool hsrc = LF_SRC(fl[h]);
+    int32_t own = c, rv = c;
+    if (saturate && src != hsrc) {
+      own = src ? 0 : 2 * c;
+      rv = src ? 2 * c : 0;
+      atomicAdd(A.ex + vb + (src ? h : i), c);
+    }
+    L[at] = row_word(own, rv, h, t);
+    L[row_index(L, nr, h, t)] = row_word(rv, own, i, s);
+  }
+}
+
 template <typename Items>
 __device__ __forceinline__ void net_rev(const KArgs &A, Items &&items) {
   items([&](int32_t p, int64_t item64) {
@@ -1715,7 +1857,9 @@ __device__ __forceinline__ void net_rev(const KArgs &A, Items &&items) {
     const uint32_t f = on ? fl[item] : 0u;
     const bool src = on && LF_SRC(f);
     const bool snk = on && LF_SNK(f);
-    const int32_t b0 = on ? lo[item] : 0, e0 = on ? lo[item + 1] : 0;
+    const bool rows = on && rows_chosen(A, p);
+    if (rows) net_rev_row(A, p, item, src, !A.terminals && !overflow);
+    const int32_t b0 = on && !rows ? lo[item] : 0, e0 = on && !rows ? lo[item + 1] : 0;
     int64_t ex = 0;
     for (int32_t ar = b0; ar < e0; ar++) {
       const int32_t j = arc[ar].lh;
@@ -1744,8 +1888,8 @@ __device__ __forceinline__ void net_rev(const KArgs &A, Items &&items) {
       }
     }
     if (on) {
-      if (!A.terminals) A.ex[vb + item] = src ? 0 : (int32_t)ex;  // else: the s -> u capacity
-      A.ins[vb + item] = 0;
+      // (contracted terminals: the s -> u capacity)
+      if (!A.terminals && !rows) A.ex[vb + item] = src ? 0 : (int32_t)ex;
       if (overflow) {
         A.ctl->err = FR_E_OVERFLOW;
         A.ctl->diag = DIAG_OVERFLOW;
@@ -1761,354 +1905,7 @@ __global__ void __launch_bounds__(256) k_net_rev(KArgs A, int32_t it) {
   net_rev(A, [&](auto &&f) { grid_items(A, A.cpre, f); });
 }
 
-// ---- maximum preflow, smallest source set, balance check, write-back and
-//      the adaptive factor (Sec. 4.1), one workgroup per pair.
-//      lc (sliced rounds): this launch's running and started flow entries.
-template <int TPB>
-__device__ __forceinline__ void flow_pair(const KArgs &A, int32_t p, SolveShared<TPB> &sh,
-                                          PairState &st, const int32_t *lc = nullptr) {
-  const PairView V = make_view(A, p);
-  const int32_t a = V.a, b = V.b;
-  int64_t *pa = A.pacc + (int64_t)p * PA_N;
-  if (threadIdx.x == 0) {
-    st = A.ps[p];
-    sh.cnt[0] = sh.cnt[1] = sh.cnt[2] = 0;
-    sh.nsnk = min(A.pcnt[A.P + p], (int32_t)V.nv);
-    if (st.phase == 0) {  // a new solve (else it continues from a sliced launch)
-      st.solve_sweeps = 0;
-      st.rp_eff = A.relabel_period;
-    }
-  }
-  if (threadIdx.x < W_COUNT) sh.work[threadIdx.x] = 0ull;
-  __syncthreads();
-  const int32_t nr = uni(st.nr);
-  int64_t t0 = wall_clock64(), t1;
-  const int64_t t_start = t0;
-  bool sliced = false;
-  int64_t t_rel = 0, t_push = 0;
-  const int32_t NL = nr + 2;
-  const bool lds = nr <= 32 * FR_BM_WORDS;
-  const int32_t nw = (nr + 31) >> 5;
-  const bool overflow = pa[PA_RCAP] >= 0x7fffffffLL;
-  Rot R;
-  int64_t gr_levels = 0, sweeps = 0, relabels = 0, cl_levels = 0;
-  if (!overflow) {
-    // one relabel call site (the relabel is inlined; one copy keeps the
-    // kernel within its registers): at the start, when the active list
-    // runs dry and after rp_eff passes
-    int32_t cnt = 0;
-    ListRef cur, nxt;
-    int since = 0;
-    // sweeps until the next global relabel: half the last relabel's BFS
-    // depth (a deep corridor's relabel costs more), within [period / 4,
-    // 2 period] of the tuning's period
-    int32_t rp_eff = uni(st.rp_eff);
-    const int32_t rp_lo = max(1, A.relabel_period / 4), rp_hi = 2 * A.relabel_period;
-    const int64_t sweeps0 = uni(st.solve_sweeps);  // of this solve, in earlier launches
-    bool relabel = true;
-    for (;;) {
-      if (relabel && A.slice_ticks > 0 && relabels > 0) {
-        // sliced rounds: once this launch's time is used up, stop where a
-        // global relabel is due anyway; the next launch starts with it
-        // (only while at most a quarter of the launch's entries still run:
-        // the others are waiting for it)
-        if (threadIdx.x == 0) {
-          int32_t stop = 0;
-          if (lc && wall_clock64() - t_start >= A.slice_ticks) {
-            const int32_t run = __hip_atomic_load(lc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const int32_t sta =
-                __hip_atomic_load(lc + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            stop = 4 * run <= sta ? 1 : 0;
-          }
-          sh.slice_end = stop;
-        }
-        __syncthreads();
-        sliced = uni(sh.slice_end) != 0;
-        __syncthreads();
-        if (sliced) break;
-      }
-      if (relabel) {
-        t1 = wall_clock64();
-        t_push += t1 - t0;
-        t0 = t1;
-        {
-          const int64_t lev0 = gr_levels;
-          cnt = global_relabel<TPB>(A, V, nr, NL, sh, R, gr_levels, lds);
-          rp_eff = (int32_t)min((int64_t)rp_hi, max((int64_t)rp_lo, (gr_levels - lev0) / 2));
-        }
-        t1 = wall_clock64();
-        t_rel += t1 - t0;
-        t0 = t1;
-        relabels++;
-        cur = flist(V, sh, 0, lds);
-        nxt = flist(V, sh, 1, lds);
-        since = 0;
-        relabel = false;
-      }
-      if (cnt == 0) {
-        if (since == 0) break;  // an exact relabel found no active vertex
-        relabel = true;
-        continue;
-      }
-      if (sweeps0 + sweeps >= A.max_sweeps) {
-        if (threadIdx.x == 0) {
-          A.ctl->err = FR_E_SOLVER_LIMIT;
-          A.ctl->diag = DIAG_SWEEPS;
-        }
-        break;
-      }
-      // queued marks of this pass in bm[(since + 1) & 1]; the other bitmap
-      // (the previous pass's marks, or the relabel's visited marks) is
-      // cleared now and serves the next pass
-      uint32_t *qbm = nullptr;
-      if (lds) {
-        qbm = sh.u.f.bm[(since + 1) & 1];
-        uint32_t *old = sh.u.f.bm[since & 1];
-        for (int w = threadIdx.x; w < nw; w += TPB) old[w] = 0u;
-      }
-      pr_sweep_any<TPB>(A, V, cur, cnt, nxt, &sh.cnt[(R.c + 1) % 3], NL, sh.work, qbm);
-      if (threadIdx.x == 0) sh.cnt[(R.c + 2) % 3] = 0;
-      __syncthreads();
-      R.c = (R.c + 1) % 3;
-      cnt = uni(min(sh.cnt[R.c], (int32_t)V.nv));
-      const ListRef t = cur;
-      cur = nxt;
-      nxt = t;
-      sweeps++;
-      if (++since >= rp_eff) relabel = true;
-    }
-    t1 = wall_clock64();
-    t_push += t1 - t0;
-    t0 = t1;
-    if (sliced) {
-      // the solve continues in the next launch: its counters so far, its
-      // relabel interval; the network, labels and excesses stay in place
-      if (threadIdx.x == 0) {
-        st.sweeps += sweeps;
-        st.relabels += relabels;
-        st.gr_levels += gr_levels;
-        for (int j = 0; j < W_COUNT; j++) st.work[j] += (int64_t)sh.work[j];
-        st.t_relabel += t_rel;
-        st.t_push += t_push;
-        st.solve_sweeps = sweeps0 + sweeps;
-        st.rp_eff = rp_eff;
-        st.phase = 1;
-        st.slices++;
-        A.ps[p] = st;
-      }
-      __syncthreads();
-      return;
-    }
-    // ---- smallest source set (Sec. 4.1.1): closure of the source border
-    //      and of every vertex left with excess, over arcs with residual
-    //      capacity
-    {
-      uint32_t *vis = sh.u.f.bm[0];
-      cur = flist(V, sh, 0, lds);
-      nxt = flist(V, sh, 1, lds);
-      int32_t *ncnt = &sh.cnt[(R.c + 1) % 3];
-      BLOCK_WAVE_LOOP(i, nr) {
-        bool seed = false;
-        if (i < nr) {
-          const uint32_t f = V.fl[i];
-          seed = LF_SRC(f) || (!LF_SNK(f) && V.ex[i] > 0);
-          if (seed) V.ins[i] = 1;
-        }
-        if (lds) {
-          const unsigned long long m = __ballot(seed);
-          if (lane64() == 0) vis[i >> 5] = (uint32_t)m;
-          if (lane64() == 32) vis[i >> 5] = (uint32_t)(m >> 32);
-        }
-        const int pos = wave_append(ncnt, seed);
-        if (seed) lput(cur, pos, V.nv, (int32_t)i, A.ctl);
-      }
-      if (threadIdx.x == 0) sh.cnt[(R.c + 2) % 3] = 0;
-      __syncthreads();
-      R.c = (R.c + 1) % 3;
-      int32_t cnt2 = uni(min(sh.cnt[R.c], (int32_t)V.nv));
-      while (cnt2 > 0) {
-        int32_t *ncnt2 = &sh.cnt[(R.c + 1) % 3];
-        for_groups<GTF>(cnt2, [&](int item, bool valid, int gl) {
-          const int32_t u = valid ? lget(cur, item) : 0;
-          const int32_t e0 = valid ? V.lo[u] : 0, e1 = valid ? V.lo[u + 1] : 0;
-          count_work(sh, W_CL_ITEMS, (valid && gl == 0) ? 1 : 0);
-          count_work(sh, W_CL_ARCS, (valid && gl == 0) ? e1 - e0 : 0);
-          for (int32_t c0 = e0; c0 < e1; c0 += GTF * KF) {
-            int32_t v[KF], r[KF];
-#pragma unroll
-            for (int k = 0; k < KF; k++) {
-              const int32_t ar = c0 + k * GTF + gl;
-              Arc x = {0, 0, 0ull};
-              if (ar < e1) x = V.arc[ar];
-              r[k] = res_own(x.rc);
-              v[k] = x.lh;
-            }
-#pragma unroll
-            for (int k = 0; k < KF; k++) {
-              bool claim = false;
-              if (r[k] > 0) {
-                if (lds) {
-                  const bool seen = (vis[v[k] >> 5] >> (v[k] & 31)) & 1u;
-                  if (!seen) {
-                    claim = bm_claim(vis, v[k]);
-                    if (claim) V.ins[v[k]] = 1;
-                  }
-                } else if (V.ins[v[k]] == 0) {
-                  claim = atomicCAS(&V.ins[v[k]], 0, 1) == 0;
-                }
-              }
-              const int pos = wave_append(ncnt2, claim);
-              if (claim) lput(nxt, pos, V.nv, v[k], A.ctl);
-            }
-          }
-        });
-        if (threadIdx.x == 0) sh.cnt[(R.c + 2) % 3] = 0;
-        __syncthreads();
-        R.c = (R.c + 1) % 3;
-        cnt2 = uni(min(sh.cnt[R.c], (int32_t)V.nv));
-        const ListRef t = cur;
-        cur = nxt;
-        nxt = t;
-        cl_levels++;
-      }
-    }
-  }
-  t1 = wall_clock64();
-  const int64_t t_cl = t1 - t0;
-  t0 = t1;
-  // ---- candidate partition and its balance check (Sec. 2.1); for the most
-  //      balanced cut, also the free vertices (neither in the smallest
-  //      source set nor able to reach the sink: exact label NL), listed in
-  //      LB with LA[i] = i for them and -1 for every other corridor vertex
-  // flow, moved a->b, moved b->a, source side; the same three for the
-  // largest minimum source side (label >= NL: cannot reach the sink)
-  int64_t acc[7] = {0, 0, 0, 0, 0, 0, 0};
-  const bool term = A.terminals != 0;
-  const bool mb = A.mb_reps > 0 && !overflow;
-  const int side_mode = (A.mb_reps > 0 || overflow) ? 0 : A.cut_side;
-  if (mb) {
-    if (threadIdx.x == 0) sh.nfree = 0;
-    __syncthreads();
-  }
-  if (!overflow) {
-    BLOCK_WAVE_LOOP(i, nr) {
-      bool fv = false;
-      if (i < nr) {
-        const uint32_t f = V.fl[i];
-        const int32_t w = A.vwgt[V.lg[i]];
-        const bool in = V.ins[i] != 0;
-        // the closure reached the sink: the preflow was not maximal
-        if (in && (term ? V.SNK[i] > 0 : LF_SNK(f))) {
-          A.ctl->err = FR_E_DEVICE;
-          A.ctl->diag = DIAG_CLOSURE;
-        }
-        // flow: what reached the sink border; contracted terminals: what
-        // left s and stayed nowhere in the corridor
-        if (term) acc[0] -= V.ex[i];
-        else if (LF_SNK(f)) acc[0] += V.ex[i];
-        if (!(f & LF_SIDE_B) && !in) acc[1] += w;
-        if ((f & LF_SIDE_B) && in) acc[2] += w;
-        acc[3] += in ? 1 : 0;
-        if (side_mode) {
-          const bool inx = V.lab[i] >= NL;
-          if (!(f & LF_SIDE_B) && !inx) acc[4] += w;
-          if ((f & LF_SIDE_B) && inx) acc[5] += w;
-          acc[6] += inx ? 1 : 0;
-        }
-        if (mb) {
-          fv = !in && !(f & LF_BORDER) && V.lab[i] == NL;
-          V.LA[i] = fv ? (int32_t)i : -1;
-        }
-      }
-      if (mb) {
-        const int pos = wave_append(&sh.nfree, fv);
-        if (fv) V.LB[pos] = (int32_t)i;
-      }
-    }
-  }
-  block_sums<7>(acc, sh.red);
-  // the record of this solve; the adaptive rule and the write-back run in
-  // k_select, over all slots of the pair
-  if (threadIdx.x == 0) {
-    st.sweeps += sweeps;
-    st.relabels += relabels;
-    st.gr_levels += gr_levels;
-    st.cl_levels += cl_levels;
-    for (int j = 0; j < W_COUNT; j++) st.work[j] += (int64_t)sh.work[j];
-    st.t_relabel += t_rel;
-    st.t_push += t_push;
-    st.t_closure += t_cl;
-    fr_solve rec;
-    const int64_t cut = st.cut;
-    rec.alpha = st.alpha;
-    if (term) acc[0] += pa[PA_CS];
-    rec.flow = acc[0];
-    rec.region_vertices = nr;
-    rec.region_edges = pa[PA_RARCS] / 2;
-    rec.source_side = acc[3];
-    rec.cut_before = cut;
-    int64_t cand = cut - pa[PA_RCIN] + acc[0];
-    int64_t wa = st.cA - acc[1] + acc[2];
-    int64_t wb = st.cB + acc[1] - acc[2];
-    sh.use_max = 0;
-    if (side_mode && cut != 0) {  // the largest minimum source side instead
-      const int64_t wa2 = st.cA - acc[4] + acc[5], wb2 = st.cB + acc[4] - acc[5];
-      const bool f1 = wa <= A.lmax && wb <= A.lmax, f2 = wa2 <= A.lmax && wb2 <= A.lmax;
-      if (side_mode == 1 || (!f1 && f2)) {
-        sh.use_max = 1;
-        wa = wa2;
-        wb = wb2;
-        rec.source_side = acc[6];
-      }
-    }
-    int dec;
-    if (cut == 0) {
-      dec = FR_DEC_NOT_ADJACENT;
-      cand = 0;
-      wa = st.cA;
-      wb = st.cB;
-      rec.flow = 0;
-    } else {
-      const bool feas = wa <= A.lmax && wb <= A.lmax;
-      dec = !feas ? FR_DEC_INFEASIBLE : (cand < cut ? FR_DEC_APPLY : FR_DEC_EQUAL);
-    }
-    rec.cut_candidate = cand;
-    rec.wa = wa;
-    rec.wb = wb;
-    rec.decision = dec;
-    A.srec[p] = rec;
-    st.t_finish += wall_clock64() - t0;
-    for (int j = 0; j < PA_N; j++) pa[j] = 0;
-    A.pcnt[p] = mb ? sh.nfree : 0;  // the most balanced cut kernel reads and clears it
-    A.pcnt[A.P + p] = 0;
-    st.phase = 2;
-    A.ps[p] = st;
-  }
-  __syncthreads();
-  if (sh.use_max) {  // the source side becomes every vertex that cannot reach the sink
-    BLOCK_WAVE_LOOP(i, nr) {
-      if (i < nr) V.ins[i] = V.lab[i] >= NL ? 1 : 0;
-    }
-    __syncthreads();
-  }
-}
-
-template <int TPB>
-__global__ void __launch_bounds__(TPB) k_flow(KArgs A, int32_t it) {
-  __shared__ SolveShared<TPB> sh;
-  __shared__ PairState st;
-  for (;;) {
-    int32_t *lc = A.queue + 4 * (it % A.max_iters) + 2;  // running, started
-    const int32_t p = next_pair<TPB>(A, lc - 1, sh, 1);
-    if (p < 0) break;
-    if (threadIdx.x == 0 && A.slice_ticks > 0) {
-      atomicAdd(lc, 1);
-      atomicAdd(lc + 1, 1);
-    }
-    flow_pair<TPB>(A, p, sh, st, lc);
-    if (threadIdx.x == 0 && A.slice_ticks > 0) atomicSub(lc, 1);
-  }
-}
+#include "fr_flow.h"
 
 // ---- the adaptive factor (Sec. 4.1), one block per pair: walk the slots
 //      solved in this launch in halving order as the sequential loop would
@@ -2224,7 +2021,8 @@ __global__ void __launch_bounds__(1024) k_select(KArgs A, int32_t it) {
 
 // ---- a whole round in one launch: each workgroup takes a pair (one entry
 //      per pair, W = 1) and runs its adaptive loop -- boundary, corridor,
-//      network, flow, the adaptive rule -- to the end without waiting for the
+//      network (CSR form: its launch sets row_nr to -1), flow, the adaptive
+//      rule -- to the end without waiting for the
 //      other pairs.  The phases are the bodies of the per-iteration kernels
 //      over the pair's own items; a pair's buffers are touched by its
 //      workgroup only, so barriers order the phases.
@@ -2250,7 +2048,7 @@ __global__ void __launch_bounds__(TPB) k_round(KArgs A) {
       __syncthreads();
       net_rev(A, [&](auto &&f) { pair_items(p, nr, f); });
       __syncthreads();
-      flow_pair<TPB>(A, p, sh, st);
+      flow_pair<TPB, false>(A, p, sh, st);
       __syncthreads();
       select_pair(A, p, s_sel);
       __syncthreads();

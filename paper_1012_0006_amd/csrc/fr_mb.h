@@ -332,6 +332,34 @@ __global__ void __launch_bounds__(256) k_mb_union(KArgs A, int32_t it) {
     const Arc *arc = A.arc + ab;
     int32_t *w1 = A.mbq + ab;
     const int32_t u = A.LB[vb + (i - A.mpre[p])];
+    if (A.ps[p].rows) {
+      const u64 *L = rows_of(A, p);
+      const int32_t nr = A.ps[p].nr;
+      const int32_t deg = (int32_t)(L[(int64_t)ROW_WORDS * u] >> 32);
+      for (int32_t s0 = 0; s0 < deg; s0 += MBK) {
+        u64 x[MBK];
+        int64_t at[MBK];
+        int32_t pv[MBK];
+#pragma unroll
+        for (int k = 0; k < MBK; k++) {
+          at[k] = row_index(L, nr, u, min(s0 + k, deg - 1));
+          x[k] = L[at[k]];
+        }
+#pragma unroll
+        for (int k = 0; k < MBK; k++)
+          pv[k] = s0 + k < deg && row_own(x[k]) > 0 ? par[row_head(x[k])] : -1;
+#pragma unroll
+        for (int k = 0; k < MBK; k++) {
+          if (pv[k] < 0) continue;
+          if (row_rev(x[k]) > 0) {
+            if (row_head(x[k]) > u) uf_union(par, u, row_head(x[k]));
+          } else {
+            w1[atomicAdd(A.pcnt + A.P + p, 1)] = (int32_t)at[k];
+          }
+        }
+      }
+      continue;
+    }
     const int32_t e1 = lo[u + 1];
     for (int32_t c0 = lo[u]; c0 < e1; c0 += MBK) {
       Arc x[MBK];
@@ -463,9 +491,20 @@ __global__ void __launch_bounds__(MB_TPB) k_mb(KArgs A, int32_t it) {
   int32_t *qoff = lq ? sh.u2.q.qoff : V.ex;
   for (int32_t q = threadIdx.x; q < nq; q += blockDim.x) qoff[q] = 0;
   __syncthreads();
+  const bool rows = A.ps[p].rows != 0;
   auto one_way = [&](int32_t j, auto &&f) {
-    const Arc x = V.arc[w1[j]];
-    const int32_t ru = par[V.arc[x.lr].lh], rv = par[x.lh];
+    int32_t tail, head;  // the listed arc's ends: its reverse arc points at the tail
+    if (rows) {
+      const u64 *L = rows_of(A, p);
+      const u64 x = L[w1[j]];
+      head = row_head(x);
+      tail = row_head(L[row_index(L, nr, head, row_rslot(x))]);
+    } else {
+      const Arc x = V.arc[w1[j]];
+      head = x.lh;
+      tail = V.arc[x.lr].lh;
+    }
+    const int32_t ru = par[tail], rv = par[head];
     if (ru != rv) f(qid[ru], qid[rv]);
   };
   for (int32_t j = threadIdx.x; j < n1w; j += blockDim.x)

@@ -141,13 +141,17 @@ struct RowSolver {
   Labels<LL> lab;
   uint32_t *bm0, *bm1;
   int32_t *ls;  // LDS heads of the two lists
+  const int32_t wave;
   int32_t from = 1, c_next = 1;  // list read, counter of the list written
   // vertices and arcs touched by this thread's lanes: passes, relabels, closure
-  int32_t wi[3] = {0, 0, 0}, wa[3] = {0, 0, 0};
+  int32_t wi = 0, wa[3] = {0, 0, 0};
+  int32_t gr_items = 0, cl_items = 0;
+  uint32_t ahead = 0;
 
   __device__ __forceinline__ RowSolver(const KArgs &A_, const PairView &V_, SolveShared<TPB> &sh_,
                                        u64 *L_, int32_t nr_)
-      : A(A_), V(V_), sh(sh_), L(L_), nr(nr_), NL(nr_ + 2) {
+      : A(A_), V(V_), sh(sh_), L(L_), nr(nr_), NL(nr_ + 2),
+        wave(uni((int32_t)threadIdx.x >> 6)) {
     unsigned char *mem = reinterpret_cast<unsigned char *>(&sh.u);
     ls = reinterpret_cast<int32_t *>(mem);
     bm0 = reinterpret_cast<uint32_t *>(mem + 8 * FR_LDS_LIST);
@@ -168,16 +172,20 @@ struct RowSolver {
   // The frontier lists: slots 0 and 1 (their first FR_LDS_LIST entries in
   // LDS); `from` is read, the other one written.  from = 2: the sink list
   // (global memory), slot 0 written.
-  __device__ __forceinline__ int32_t get(int32_t item, bool valid, int32_t limit) const {
-    const int32_t ns = from == 2 ? 0 : FR_LDS_LIST;
+  __device__ __forceinline__ int32_t get(int32_t item, bool valid, bool in_lds) const {
     const int32_t *s = ls + (from & 1) * FR_LDS_LIST;
-    if (limit <= ns) return s[item];
+    if (in_lds) return s[item];
     // two loads and a select: a load through a selected pointer would be a
     // flat one, which waits for both memories
+    const int32_t ns = from == 2 ? 0 : FR_LDS_LIST;
     const int32_t *g = from == 2 ? V.SNK : (from ? V.LB : V.LA);
     const int32_t a = s[min(item, FR_LDS_LIST - 1)];
     const int32_t b = valid && item >= ns ? g[item] : 0;
     return item < ns ? a : b;
+  }
+  // the whole list (cnt entries, read up to a wave's groups past its end) in LDS
+  __device__ __forceinline__ bool list_in_lds(int32_t cnt) const {
+    return from != 2 && cnt <= FR_LDS_LIST - WAVE;
   }
   template <int K>
   __device__ __forceinline__ void append(const bool (&want)[K], const int32_t (&v)[K]) {
@@ -188,30 +196,33 @@ struct RowSolver {
 
   // End of a step: the written list becomes the one to read; its length.
   __device__ __forceinline__ int32_t advance() {
-    const int32_t c_clear = c_next == 2 ? 0 : c_next + 1;
-    if (threadIdx.x == 0) sh.cnt[c_clear] = 0;
+    const int32_t c_clear = uni(c_next == 2 ? 0 : c_next + 1);
+    if (wave == 0) sh.cnt[c_clear] = 0;
     __syncthreads();
     const int32_t n = uni(min(sh.cnt[c_next], nr));
     c_next = c_clear;
-    from = from == 0 ? 1 : 0;
+    from = uni(from == 0 ? 1 : 0);
     return n;
   }
 
   // One level of a search over the list: REV = backwards (over arcs whose reverse
   // has residual capacity: v can push to w), else forwards.  Heads not yet in
   // bm0 are claimed, labelled (on request) and appended.
+  // ahead: the claimed heads' rows, touched here so that the next level finds
+  // them in L1 or on their way (kept until the next level's own loads have
+  // arrived: nothing waits for it).
   template <int G, bool REV, bool SET>
   __device__ __forceinline__ void level(int32_t cnt, int32_t d, int32_t &arcs) {
     constexpr int K = ROW_WORDS / G;
-    const int32_t tid = step_tid();
-    const int gl = tid & (G - 1);
-    const int wf = uni(tid & ~63) / G, gid = tid / G;
+    const int wf = wave * (WAVE / G);
+    if (wf >= cnt) return;  // straight to the step's barrier
+    const int32_t ln = step_lane();
+    const int gl = ln & (G - 1), grp = ln / G;
     auto claim_words = [&](const u64 (&x)[K]) {
       // the marks of all K heads in flight together (no look before the
       // atomic: it would cost a second LDS round trip per step)
       int32_t h[K];
       uint32_t bit[K], old[K];
-      bool claim[K];
 #pragma unroll
       for (int k = 0; k < K; k++) {
         h[k] = row_head(x[k]);
@@ -219,17 +230,45 @@ struct RowSolver {
         old[k] = ~0u;
         if ((REV ? row_rev(x[k]) : row_own(x[k])) > 0) old[k] = atomicOr(&bm0[h[k] >> 5], bit[k]);
       }
+      u64 m[K];
+      int32_t total = 0;
 #pragma unroll
       for (int k = 0; k < K; k++) {
-        claim[k] = !(old[k] & bit[k]);
-        if (SET && claim[k]) lab.set(h[k], d);
+        m[k] = ballot64(!(old[k] & bit[k]));
+        total += (int32_t)__popcll(m[k]);
       }
-      append(claim, h);
+      if (total == 0) return;
+      int32_t at = 0;
+      if (ln == 0) at = atomicAdd(&sh.cnt[c_next], total);
+      at = uni(at);
+      const int to = from == 0 ? 1 : 0;
+      int32_t *s = ls + to * FR_LDS_LIST;
+      const bool fits = at + total <= FR_LDS_LIST;
+#pragma unroll
+      for (int k = 0; k < K; k++) {
+        const int32_t pos = at + lanes_below(m[k]);
+        if (!(old[k] & bit[k])) {
+          if (SET) lab.set(h[k], d);
+          if (fits || pos < FR_LDS_LIST) s[pos] = h[k];
+          ahead = *reinterpret_cast<const uint32_t *>(L + (int64_t)ROW_WORDS * h[k]);
+        }
+        at += (int32_t)__popcll(m[k]);
+      }
+      if (!fits) {  // the part of the list beyond LDS
+        int32_t *g = to ? V.LB : V.LA;
+#pragma unroll
+        for (int k = K - 1; k >= 0; k--) {
+          at -= (int32_t)__popcll(m[k]);
+          const int32_t pos = at + lanes_below(m[k]);
+          if (!(old[k] & bit[k]) && pos >= FR_LDS_LIST) put_bounded(g, pos, V.nv, h[k], A.ctl);
+        }
+      }
     };
+    const bool in_lds = list_in_lds(cnt);
     for (int base = wf; base < cnt; base += TPB / G) {
-      const int item = base + (gid - wf);
+      const int item = base + grp;
       const bool valid = item < cnt;
-      const int32_t w = get(item, valid, base + WAVE / G);
+      const int32_t w = get(item, valid, in_lds);
       u64 x[K];
       row_load<K>(L, w, gl, valid, x);
       int32_t deg = 0, ovf = 0;
@@ -239,6 +278,7 @@ struct RowSolver {
         x[0] = 0ull;
       }
       arcs += deg;
+      asm volatile("" ::"v"(ahead));
       claim_words(x);
       if (__any(deg > ROW_SLOTS)) {
         const int32_t more = group_first<G>(row_overflow(deg));
@@ -292,7 +332,7 @@ struct RowSolver {
       lev = 0;
     }
     while (cnt > 0) {
-      if (threadIdx.x == 0) wi[1] += cnt;
+      gr_items += cnt;
       by_row_width<TPB>(cnt, [&](auto W) {
         level<decltype(W)::g, true, true>(cnt, lev + 1, wa[1]);
       });
@@ -330,24 +370,34 @@ struct RowSolver {
 
   // One push/relabel pass over the list with G lanes per vertex (as pr_sweep:
   // residuals and excess change by atomics, labels only grow).  A vertex that
-  // received flow or stays active joins the next list once: the first lane to mark it
-  // in qbm queues it.  old: the previous pass's marks, cleared item by item.
+  // received flow or stays active joins the next list once: the first lane to
+  // mark it in qbm queues it.  old_bm: the previous pass's marks, cleared item
+  // by item.
+  //
+  // A vertex pushes along the arcs below its label d; with excess left it is
+  // relabelled to one above its lowest residual neighbour and pushes along the
+  // arcs to that level too.  Both amounts are known before anything is
+  // written, so an arc gets its atomics once.  Wide lists are bound by the
+  // instructions issued (16 waves share 4 SIMDs), narrow ones by their
+  // latency: either way a pass takes as long as its instructions.
   template <int G>
   __device__ __forceinline__ void pass_rows(int32_t cnt, uint32_t *qbm, uint32_t *old_bm) {
     constexpr int K = ROW_WORDS / G;
-    const int32_t tid = step_tid();
-    const int gl = tid & (G - 1);
-    const int wf = uni(tid & ~63) / G, gid = tid / G;
+    const int wf = wave * (WAVE / G);
+    if (wf >= cnt) return;  // straight to the step's barrier
+    const int32_t ln = step_lane();
+    const int gl = ln & (G - 1), grp = ln / G;
     const bool term = A.terminals != 0;
+    const bool in_lds = list_in_lds(cnt);
     for (int base = wf; base < cnt; base += TPB / G) {
-      const int item = base + (gid - wf);
+      const int item = base + grp;
       const bool valid = item < cnt;
-      const int32_t w = get(item, valid, base + WAVE / G);
+      const int32_t w = get(item, valid, in_lds);
       const int32_t u = valid ? w : 0;
       u64 x[K];
       row_load<K>(L, u, gl, valid, x);
-      int32_t e = valid ? V.ex[u] : 0;
-      int32_t rt = term && valid ? V.SNK[u] : 0;
+      int32_t e = valid ? *at32(V.ex, u) : 0;
+      int32_t rt = term && valid ? *at32(V.SNK, u) : 0;
       const int32_t d = lab.get(u);
       if (old_bm && valid && gl == 0) atomicAnd(&old_bm[u >> 5], ~(1u << (u & 31)));
       int32_t deg = 0, ovf = 0;
@@ -359,129 +409,146 @@ struct RowSolver {
       // the first lane's copy of the excess counts: it may grow
       // concurrently, and every lane must push against the same value
       e = group_first<G>(e);
-      if (term) rt = group_first<G>(rt);
       const bool work = valid && d < NL && e > 0;
       if (!work) deg = 0;
-      if (work && gl == 0) {
-        wi[0]++;
-        wa[0] += deg;
-      }
-      int32_t erem = work ? e : 0, pushed = 0;
+      wi += deg > 0 ? 1 : 0;
+      wa[0] += deg;
+      int32_t erem = work ? e : 0;
       // the arc to t first: always admissible (t is at label 0); once it is
       // saturated it takes no part in the relabel
-      if (term && work && rt > 0) {
-        const int32_t amt = e < rt ? e : rt;
-        if (gl == 0) V.SNK[u] = rt - amt;
+      if (term) {
+        rt = group_first<G>(rt);
+        const int32_t amt = min(erem, max(rt, 0));
+        if (gl == 0 && amt > 0) *at32(V.SNK, u) = rt - amt;
         erem -= amt;
-        pushed += amt;
       }
-      // pushes along the words of one row that are admissible for label dcur
-      // (residual left, head label below dcur), in arc order, until the
-      // excess is used up; r[] keeps the residual left, q[] the heads queued.
-      // Sums of a row's residuals stay far below 2^31.  The marks of all
-      // heads are in flight together.
-      auto push = [&](int64_t row, const u64 (&x)[K], int32_t (&r)[K], const int32_t (&dh)[K],
-                      bool (&q)[K], int32_t dcur) {
-        int32_t adm[K], amt[K], s = 0;
-#pragma unroll
-        for (int k = 0; k < K; k++) {
-          adm[k] = (r[k] > 0 && dh[k] < dcur) ? r[k] : 0;
-          s += adm[k];
-        }
-        int32_t left = erem - (group_scan<G>(s) - s);  // excess for this lane's first word
-        const int32_t tot = group_sum<G>(s);
-#pragma unroll
-        for (int k = 0; k < K; k++) {
-          amt[k] = max(0, min(adm[k], left));
-          left -= adm[k];
-          r[k] -= amt[k];
-        }
-        uint32_t old[K];
-#pragma unroll
-        for (int k = 0; k < K; k++) {
-          old[k] = ~0u;
-          if (amt[k] > 0) {
-            const u64 a = (u64)(uint32_t)amt[k];
-            const int32_t h = row_head(x[k]);
-            if (dh[k] > 0) old[k] = atomicOr(&qbm[h >> 5], 1u << (h & 31));
-            atomicAdd(&L[ROW_WORDS * row + K * gl + k], (a << 16) - a);
-            atomicAdd(&L[row_index(L, nr, h, row_rslot(x[k]))], a - (a << 16));
-            atomicAdd(&V.ex[h], amt[k]);
-          }
-        }
+      int32_t r[K], dh[K], amt[K];
+      residuals<K>(x, r, dh, work);
+      erem -= share<G, K>(r, dh, erem, amt, [&](int32_t l) { return l < d; });
+      int32_t nd = d;
+      if (__any(erem > 0)) {
+        int32_t minres = 0x7fffffff;
 #pragma unroll
         for (int k = 0; k < K; k++)
-          q[k] = q[k] || !(old[k] & (1u << (row_head(x[k]) & 31)));
-        const int32_t used = tot < erem ? tot : erem;
-        erem -= used;
-        pushed += used;
-      };
-      auto residuals = [&](const u64 (&x)[K], int32_t (&r)[K], int32_t (&dh)[K], bool (&q)[K]) {
+          if (dh[k] >= d && dh[k] < minres) minres = dh[k];
+        int32_t more = 0;
+        if (__any(deg > ROW_SLOTS && erem > 0)) {  // the overflow rows, at label d
+          more = erem > 0 ? group_first<G>(row_overflow(deg)) : 0;
+          const int64_t row0 = (int64_t)nr + group_first<G>(ovf);
+          for (int32_t j = 0; __any(j < more); j++) {
+            u64 y[K];
+            int32_t r2[K], dh2[K], amt2[K];
+            row_load<K>(L, row0 + j, gl, j < more, y);
+            residuals<K>(y, r2, dh2, j < more);
+            erem -= share<G, K>(r2, dh2, erem, amt2, [&](int32_t l) { return l < d; });
 #pragma unroll
-        for (int k = 0; k < K; k++) {
-          r[k] = work ? row_own(x[k]) : 0;
-          dh[k] = lab.get(row_head(x[k]));
-          q[k] = false;
-        }
-#pragma unroll
-        for (int k = 0; k < K; k++) dh[k] = r[k] > 0 ? dh[k] : 0x7fffffff;
-      };
-      int32_t r[K], dh[K];
-      bool q[K];
-      residuals(x, r, dh, q);
-      push(u, x, r, dh, q, d);
-      int32_t minres = 0x7fffffff;
-#pragma unroll
-      for (int k = 0; k < K; k++)
-        if (r[k] > 0 && dh[k] < minres) minres = dh[k];
-      const bool many = __any(deg > ROW_SLOTS);
-      int32_t more = 0;
-      if (many) {
-        more = group_first<G>(row_overflow(deg));
-        const int64_t row0 = (int64_t)nr + group_first<G>(ovf);
-        for (int32_t j = 0; __any(j < more); j++) {
-          u64 y[K];
-          int32_t r2[K], dh2[K], h2[K];
-          bool q2[K];
-          row_load<K>(L, row0 + j, gl, j < more, y);
-          residuals(y, r2, dh2, q2);
-          push(row0 + j, y, r2, dh2, q2, d);
-#pragma unroll
-          for (int k = 0; k < K; k++) {
-            if (r2[k] > 0 && dh2[k] < minres) minres = dh2[k];
-            h2[k] = row_head(y[k]);
+            for (int k = 0; k < K; k++)
+              if (dh2[k] >= d && dh2[k] < minres) minres = dh2[k];
+            send<G, K>(row0 + j, gl, y, dh2, amt2, qbm, -1);
           }
-          append(q2, h2);
+        }
+        minres = group_min<G>(minres);
+        if (erem > 0) {
+          const int32_t cand = minres >= NL ? NL : minres + 1;
+          if (cand > d) nd = cand;
+        }
+        if (gl == 0 && nd > d) lab.set(u, nd);
+        // (a vertex whose arcs fit its own row still holds them)
+        const bool second = nd > d && nd < NL && more == 0;
+        if (__any(second)) {
+          int32_t amt2[K];
+          erem -= share<G, K>(r, dh, second ? erem : 0, amt2,
+                              [&](int32_t l) { return l >= d && l < nd; });
+#pragma unroll
+          for (int k = 0; k < K; k++) amt[k] += amt2[k];
         }
       }
-      minres = group_min<G>(minres);
-      // relabel to one above the lowest residual neighbour
-      int32_t nd = d;
-      if (work && erem > 0) {
-        const int32_t cand = minres >= NL ? NL : minres + 1;
-        if (cand > d) nd = cand;
-      }
-      if (work && gl == 0 && nd > d) lab.set(u, nd);
-      // discharge on: after a relabel the arcs to the lowest neighbours are
-      // admissible; a vertex whose arcs fit its own row still holds them
-      const bool second = work && erem > 0 && nd > d && nd < NL && more == 0;
-      if (__any(second)) push(u, x, r, dh, q, second ? nd : INT32_MIN);
-      bool want[K + 1];
-      int32_t v[K + 1];
-#pragma unroll
-      for (int k = 0; k < K; k++) {
-        want[k] = q[k];
-        v[k] = row_head(x[k]);
-      }
-      want[K] = false;
-      v[K] = u;
+      int32_t again = -1;
       if (work && gl == 0) {
+        if (e > erem) atomicSub(at32(V.ex, u), e - erem);
         // flow pushed into u during this pass queued u already
-        if (pushed > 0) atomicSub(&V.ex[u], pushed);
-        want[K] = e - pushed > 0 && nd < NL && bm_claim(qbm, u);
+        if (erem > 0 && nd < NL && bm_claim(qbm, u)) again = u;
       }
-      append(want, v);
+      send<G, K>(u, gl, x, dh, amt, qbm, again);
     }
+  }
+
+  // p[i] of an array below 4 GB: a scalar base and a 32-bit offset
+  static __device__ __forceinline__ int32_t *at32(int32_t *p, int32_t i) {
+    return reinterpret_cast<int32_t *>(reinterpret_cast<char *>(p) + (uint32_t)i * 4u);
+  }
+  __device__ __forceinline__ u64 *word_at(uint32_t i) const {
+    return reinterpret_cast<u64 *>(reinterpret_cast<char *>(L) + i * 8u);
+  }
+
+  // own residuals of a row's words and their heads' labels (a large label
+  // where nothing is left)
+  template <int K>
+  __device__ __forceinline__ void residuals(const u64 (&x)[K], int32_t (&r)[K], int32_t (&dh)[K],
+                                            bool on) const {
+#pragma unroll
+    for (int k = 0; k < K; k++) {
+      r[k] = on ? row_own(x[k]) : 0;
+      dh[k] = lab.get(row_head(x[k]));
+    }
+#pragma unroll
+    for (int k = 0; k < K; k++) dh[k] = r[k] > 0 ? dh[k] : 0x7fffffff;
+  }
+
+  // Splits the group's excess e over the words with take(label), in arc
+  // order: amt[] per word; returns the sum.  (Sums of a row's residuals stay
+  // far below 2^31.)
+  template <int G, int K, typename Take>
+  static __device__ __forceinline__ int32_t share(const int32_t (&r)[K], const int32_t (&dh)[K],
+                                                  int32_t e, int32_t (&amt)[K], Take &&take) {
+    int32_t adm[K], s = 0;
+#pragma unroll
+    for (int k = 0; k < K; k++) {
+      adm[k] = take(dh[k]) ? r[k] : 0;
+      s += adm[k];
+    }
+    int32_t left = e - (group_scan<G>(s) - s);  // for this lane's first word
+#pragma unroll
+    for (int k = 0; k < K; k++) {
+      amt[k] = max(0, min(adm[k], left));
+      left -= adm[k];
+    }
+    return min(e, group_sum<G>(s));
+  }
+
+  // The pushes amt[] along a row's words: both residuals, the heads' excess,
+  // and the heads not queued yet (sink border apart) to the next list, with
+  // vertex `again` if it is one.  The marks of all heads are in flight
+  // together.
+  template <int G, int K>
+  __device__ __forceinline__ void send(int64_t row, int gl, const u64 (&x)[K],
+                                       const int32_t (&dh)[K], const int32_t (&amt)[K],
+                                       uint32_t *qbm, int32_t again) {
+    uint32_t old[K];
+    int32_t v[K + 1];
+#pragma unroll
+    for (int k = 0; k < K; k++) {
+      old[k] = ~0u;
+      v[k] = row_head(x[k]);
+      if (amt[k] > 0) {
+        const u64 a = (u64)(uint32_t)amt[k];
+        const uint32_t h = (uint32_t)v[k];
+        if (dh[k] > 0) old[k] = atomicOr(&qbm[h >> 5], 1u << (h & 31));
+        atomicAdd(word_at(ROW_WORDS * (uint32_t)row + K * gl + k), (a << 16) - a);
+        uint32_t slot = (uint32_t)row_rslot(x[k]);
+        uint32_t at = ROW_WORDS * h + 1u + slot;
+        if (slot >= ROW_SLOTS)
+          at = ROW_WORDS * ((uint32_t)nr + (uint32_t)*word_at(ROW_WORDS * h)) + slot - ROW_SLOTS;
+        atomicAdd(word_at(at), a - (a << 16));
+        atomicAdd(at32(V.ex, v[k]), amt[k]);
+      }
+    }
+    bool want[K + 1];
+#pragma unroll
+    for (int k = 0; k < K; k++) want[k] = !(old[k] & (1u << (v[k] & 31)));
+    want[K] = again >= 0;
+    v[K] = again;
+    append(want, v);
   }
 
   __device__ __forceinline__ int32_t pass(int32_t cnt, int32_t since) {
@@ -514,7 +581,7 @@ struct RowSolver {
     }
     int32_t cnt = advance();
     while (cnt > 0) {
-      if (threadIdx.x == 0) wi[2] += cnt;
+      cl_items += cnt;
       by_row_width<TPB>(cnt, [&](auto W) { level<decltype(W)::g, false, false>(cnt, 0, wa[2]); });
       cnt = advance();
       levels++;
@@ -528,11 +595,11 @@ struct RowSolver {
   }
 
   __device__ __forceinline__ void count_work_done() {
-    count_work(sh, W_SWEEP_ITEMS, wi[0]);
+    count_work(sh, W_SWEEP_ITEMS, wi);
     count_work(sh, W_SWEEP_ARCS, wa[0]);
-    count_work(sh, W_GR_ITEMS, wi[1]);
+    count_work(sh, W_GR_ITEMS, threadIdx.x == 0 ? gr_items : 0);
     count_work(sh, W_GR_ARCS, wa[1]);
-    count_work(sh, W_CL_ITEMS, wi[2]);
+    count_work(sh, W_CL_ITEMS, threadIdx.x == 0 ? cl_items : 0);
     count_work(sh, W_CL_ARCS, wa[2]);
     __syncthreads();
   }

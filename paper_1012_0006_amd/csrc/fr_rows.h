@@ -113,13 +113,19 @@ __device__ __forceinline__ int32_t group_scan(int32_t x) {
   return x;
 }
 
-// The thread's index, opaque to the optimiser: what is computed from it stays
+// The lane's index, opaque to the optimiser: what is computed from it stays
 // in the step that uses it.  (Hoisted out of the solver's main loop, the lane
 // offsets of every group width together spill registers.)
-__device__ __forceinline__ int32_t step_tid() {
-  int32_t t = (int32_t)threadIdx.x;
+__device__ __forceinline__ int32_t step_lane() {
+  int32_t t = (int32_t)threadIdx.x & 63;
   asm volatile("" : "+v"(t));
   return t;
+}
+
+__device__ __forceinline__ u64 ballot64(bool p) { return __builtin_amdgcn_ballot_w64(p); }
+__device__ __forceinline__ int32_t lanes_below(u64 m) {
+  return (int32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                            __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
 // Appends the K values v[k] of each lane with want[k] set to a list whose
@@ -130,28 +136,30 @@ template <int K>
 __device__ __forceinline__ void wave_append_many(int32_t *s, int32_t *g, int64_t cap,
                                                  int32_t *counter, const bool (&want)[K],
                                                  const int32_t (&v)[K], Ctl *ctl) {
-  int32_t off[K], total = 0;
+  u64 m[K];
+  int32_t total = 0;
 #pragma unroll
   for (int k = 0; k < K; k++) {
-    const u64 m = __ballot(want[k]);
-    off[k] = total + (int32_t)__builtin_amdgcn_mbcnt_hi(
-                         (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-    total += (int32_t)__popcll(m);
+    m[k] = ballot64(want[k]);
+    total += (int32_t)__popcll(m[k]);
   }
   if (total == 0) return;
   int32_t base = 0;
-  if (lane64() == 0) base = atomicAdd(counter, total);
+  if (lanes_below(~0ull) == 0) base = atomicAdd(counter, total);
   base = uni(base);
   if (base + total <= FR_LDS_LIST) {
 #pragma unroll
-    for (int k = 0; k < K; k++)
-      if (want[k]) s[base + off[k]] = v[k];
+    for (int k = 0; k < K; k++) {
+      if (want[k]) s[base + lanes_below(m[k])] = v[k];
+      base += (int32_t)__popcll(m[k]);
+    }
     return;
   }
 #pragma unroll
   for (int k = 0; k < K; k++) {
+    const int32_t pos = base + lanes_below(m[k]);
+    base += (int32_t)__popcll(m[k]);
     if (!want[k]) continue;
-    const int32_t pos = base + off[k];
     if (pos < FR_LDS_LIST) s[pos] = v[k];
     else put_bounded(g, pos, cap, v[k], ctl);
   }
@@ -160,7 +168,8 @@ __device__ __forceinline__ void wave_append_many(int32_t *s, int32_t *g, int64_t
 // Lanes per row for `cnt` rows in a workgroup of TPB threads: 8 (a row in
 // one load per lane) while that takes one pass, else 4, else 2 -- a pass more
 // pays the step's load latency again, a narrower group only more loads in
-// flight per lane.
+// flight per lane.  (Fewer lanes also mean fewer wave instructions per row,
+// which count once all waves of a SIMD are busy.)
 template <int G>
 struct RowLanes {
   static constexpr int g = G, k = ROW_WORDS / G;
@@ -176,7 +185,9 @@ __device__ __forceinline__ void by_row_width(int32_t cnt, F &&f) {
 // The lane's K words of the row at `row` (zeros when off).
 template <int K>
 __device__ __forceinline__ void row_load(const u64 *L, int64_t row, int gl, bool on, u64 (&x)[K]) {
-  const u64x2 *R = reinterpret_cast<const u64x2 *>(L + ROW_WORDS * row + K * gl);
+  // (rows lie within 4 GB: a scalar base and a 32-bit offset)
+  const u64x2 *R = reinterpret_cast<const u64x2 *>(reinterpret_cast<const char *>(L) +
+                                                   ((uint32_t)row * 128u + (uint32_t)(8 * K * gl)));
 #pragma unroll
   for (int k = 0; k < K; k += 2) {
     u64x2 v = {0ull, 0ull};

@@ -83,6 +83,8 @@ struct DevBufs {
   Ctl *ctl = nullptr;
   // learned factor: parameters, Adam moments, gradient
   float *mlp = nullptr, *mlp_m = nullptr, *mlp_v = nullptr, *mlp_g = nullptr;
+  unsigned char *mlpbuf = nullptr;  // buffers of the network calls
+  size_t mlpcap = 0;
 };
 
 struct fr_context {
@@ -389,7 +391,7 @@ extern "C" int32_t fr_destroy(fr_context *c) {
                   d.trace,    d.ucnt,  d.voff, d.aoff,  d.fstat, d.feats,  d.probs,
                   d.base,     d.scal,  d.ctl,  d.mlp,   d.mlp_m, d.mlp_v,  d.mlp_g,
                   d.qctr,     d.pcnt,  d.pacc, d.act,   d.nact,  d.vpre,   d.cpre, d.mpre,
-                  d.srec};
+                  d.srec,     d.mlpbuf};
   for (void *q : ptrs) dfree(q);
   if (c->h_ctl) (void)hipHostFree(c->h_ctl);
   for (int i = 0; i < 4; i++)
@@ -791,8 +793,7 @@ static int32_t enqueue_round(fr_context *c, KArgs A, bool use_mlp, hipStream_t s
                        (const int64_t *)d.fstat, d.feats);
     hipLaunchKernelGGL(k_mlp_forward,
                        dim3((A.P + MLP_SAMPLES_PER_BLOCK - 1) / MLP_SAMPLES_PER_BLOCK), dim3(1024),
-                       0, st, (const float *)d.mlp, (const float *)d.feats, A.P, d.probs,
-                       (float *)nullptr);
+                       0, st, (const float *)d.mlp, (const float *)d.feats, A.P, d.probs);
     hipLaunchKernelGGL(k_alpha_from_probs, dim3((A.P + 255) / 256), dim3(256), 0, st,
                        (const float *)d.probs, A.P, A.alpha0);
   }
@@ -1618,43 +1619,70 @@ extern "C" int32_t fr_mlp_init(fr_context *c, uint64_t seed) {
 
 // Scratch for n samples: x, labels or per-class costs, probs, activations
 // (4*64), backward (5+2*64).
+// Buffers of a network call, carved from one slab that the context keeps and
+// grows on demand (it is given back by fr_destroy).
 struct MlpScratch {
-  float *x = nullptr, *probs = nullptr, *act = nullptr, *dact = nullptr, *loss = nullptr;
+  float *x = nullptr, *probs = nullptr, *loss = nullptr, *partial = nullptr;
+  double *lossp = nullptr;
   int32_t *labels = nullptr, *idx = nullptr;
   float *xb = nullptr;
   int32_t *lb = nullptr;
   float *costs = nullptr, *cb = nullptr;
-  ~MlpScratch() {
-    dfree(x); dfree(probs); dfree(act); dfree(dact); dfree(loss); dfree(labels); dfree(idx);
-    dfree(xb); dfree(lb); dfree(costs); dfree(cb);
-  }
 };
 
-static int32_t mlp_alloc(MlpScratch &s, int64_t n, int64_t batch, bool with_costs = false) {
-  const int64_t m = std::max(n, batch);
-  if (dalloc(&s.x, n * MLP_IN) || dalloc(&s.probs, m * MLP_OUT) || dalloc(&s.act, m * 4 * MLP_H) ||
-      dalloc(&s.dact, m * (MLP_OUT + 2 * MLP_H)) || dalloc(&s.loss, 1) || dalloc(&s.labels, n) ||
-      dalloc(&s.idx, std::max<int64_t>(batch, 1)) || dalloc(&s.xb, batch * MLP_IN) ||
-      dalloc(&s.lb, std::max<int64_t>(batch, 1)))
-    return FR_E_OOM;
-  if (with_costs && (dalloc(&s.costs, n * MLP_OUT) || dalloc(&s.cb, batch * MLP_OUT)))
-    return FR_E_OOM;
+static int64_t mlp_tiles(int64_t n) { return (n + MLP_TILE - 1) / MLP_TILE; }
+
+// n samples; grad_n of them in one gradient (0: forward only); batch rows
+// gathered for training (0: none)
+static int32_t mlp_alloc(fr_context *c, MlpScratch &s, int64_t n, int64_t grad_n, int64_t batch,
+                         bool with_costs = false) {
+  DevBufs &d = c->d;
+  for (int pass = 0; pass < 2; pass++) {
+    size_t off = 0;
+    auto take = [&](auto **ptr, int64_t count) {
+      off = (off + 255) & ~(size_t)255;
+      if (pass) *ptr = reinterpret_cast<std::remove_reference_t<decltype(**ptr)> *>(d.mlpbuf + off);
+      off += sizeof(**ptr) * (size_t)count;
+    };
+    take(&s.x, n * MLP_IN);
+    take(&s.probs, n * MLP_OUT);
+    take(&s.labels, n);
+    take(&s.loss, 1);
+    take(&s.partial, mlp_tiles(grad_n) * MLP_NPARAMS);
+    take(&s.lossp, mlp_tiles(grad_n));
+    take(&s.idx, batch);
+    take(&s.xb, batch * MLP_IN);
+    take(&s.lb, batch);
+    take(&s.costs, with_costs ? n * MLP_OUT : 0);
+    take(&s.cb, with_costs ? batch * MLP_OUT : 0);
+    if (pass == 0 && off > d.mlpcap) {
+      dfree(d.mlpbuf);
+      d.mlpbuf = nullptr;
+      d.mlpcap = 0;
+      if (dalloc(&d.mlpbuf, (int64_t)off) != hipSuccess) return FR_E_OOM;
+      d.mlpcap = off;
+    }
+  }
   return FR_OK;
 }
 
-// labels, or per-class costs when costs is not null
-static int32_t mlp_fwd_bwd(fr_context *c, const float *x, const int32_t *labels,
-                           const float *costs, int32_t n, MlpScratch &s, bool backward) {
-  hipStream_t st = c->cs;
+static int32_t mlp_forward(fr_context *c, const float *x, int32_t n, MlpScratch &s) {
   const int fb = (n + MLP_SAMPLES_PER_BLOCK - 1) / MLP_SAMPLES_PER_BLOCK;
-  hipLaunchKernelGGL(k_mlp_forward, dim3(fb), dim3(1024), 0, st, (const float *)c->d.mlp, x, n,
-                     s.probs, s.act);
-  if (backward) {
-    hipLaunchKernelGGL(k_mlp_backward, dim3(fb), dim3(1024), 0, st, (const float *)c->d.mlp,
-                       (const float *)s.probs, labels, costs, n, (const float *)s.act, s.dact);
-    hipLaunchKernelGGL(k_mlp_grad, dim3((MLP_NPARAMS + 255) / 256), dim3(256), 0, st, x,
-                       (const float *)s.act, (const float *)s.dact, n, c->d.mlp_g);
-  }
+  hipLaunchKernelGGL(k_mlp_forward, dim3(fb), dim3(1024), 0, c->cs, (const float *)c->d.mlp, x, n,
+                     s.probs);
+  HIPCHK(hipGetLastError());
+  return FR_OK;
+}
+
+// Gradient (into the context's mlp_g) and mean loss (into *loss, optional) of
+// n samples with labels, or with per-class costs when costs is not null.
+static int32_t mlp_gradient(fr_context *c, const float *x, const int32_t *labels,
+                            const float *costs, int32_t n, MlpScratch &s, float *loss) {
+  const int tiles = (int)mlp_tiles(n);
+  hipLaunchKernelGGL(k_mlp_grad_tiles, dim3(tiles), dim3(256), 0, c->cs, (const float *)c->d.mlp, x,
+                     labels, costs, n, s.partial, s.lossp);
+  hipLaunchKernelGGL(k_mlp_grad_sum, dim3((MLP_NPARAMS + 63) / 64), dim3(256), 0, c->cs,
+                     (const float *)s.partial, (const double *)s.lossp, tiles, n, c->d.mlp_g, loss);
   HIPCHK(hipGetLastError());
   return FR_OK;
 }
@@ -1663,10 +1691,10 @@ extern "C" int32_t fr_mlp_forward(fr_context *c, const float *x, int32_t n, floa
   if (!c || !x || !probs || n < 1 || !c->mlp_loaded) return FR_E_INVALID_ARG;
   HIPCHK(hipSetDevice(c->device));
   MlpScratch s;
-  int32_t rc = mlp_alloc(s, n, 1);
+  int32_t rc = mlp_alloc(c, s, n, 0, 0);
   if (rc) return rc;
   HIPCHK(hipMemcpyAsync(s.x, x, sizeof(float) * MLP_IN * n, hipMemcpyHostToDevice, c->cs));
-  if ((rc = mlp_fwd_bwd(c, s.x, nullptr, nullptr, n, s, false))) return rc;
+  if ((rc = mlp_forward(c, s.x, n, s))) return rc;
   HIPCHK(hipMemcpyAsync(probs, s.probs, sizeof(float) * MLP_OUT * n, hipMemcpyDeviceToHost, c->cs));
   HIPCHK(hipStreamSynchronize(c->cs));
   return FR_OK;
@@ -1676,10 +1704,10 @@ extern "C" int32_t fr_mlp_predict(fr_context *c, const float *x, int32_t n, int3
   if (!c || !x || !alpha || n < 1 || !c->mlp_loaded) return FR_E_INVALID_ARG;
   HIPCHK(hipSetDevice(c->device));
   MlpScratch s;
-  int32_t rc = mlp_alloc(s, n, 1);
+  int32_t rc = mlp_alloc(c, s, n, 0, 0);
   if (rc) return rc;
   HIPCHK(hipMemcpyAsync(s.x, x, sizeof(float) * MLP_IN * n, hipMemcpyHostToDevice, c->cs));
-  if ((rc = mlp_fwd_bwd(c, s.x, nullptr, nullptr, n, s, false))) return rc;
+  if ((rc = mlp_forward(c, s.x, n, s))) return rc;
   // the start factor of each sample, as the batch and sweep calls take it
   hipLaunchKernelGGL(k_alpha_from_probs, dim3((n + 255) / 256), dim3(256), 0, c->cs,
                      (const float *)s.probs, n, s.labels);
@@ -1698,9 +1726,13 @@ extern "C" int32_t fr_eps_to_ppm(double eps, int32_t *ppm) {
 // checks of the training targets: labels in [0, 5), or finite costs
 static bool mlp_targets_ok(const int32_t *labels, const float *costs, int32_t n) {
   if (costs) {
-    for (int64_t i = 0; i < (int64_t)n * MLP_OUT; i++)
-      if (!std::isfinite(costs[i])) return false;
-    return true;
+    uint32_t bad = 0;  // an all-ones exponent: infinity or NaN
+    for (int64_t i = 0; i < (int64_t)n * MLP_OUT; i++) {
+      uint32_t b;
+      memcpy(&b, costs + i, sizeof(b));
+      bad |= (b & 0x7f800000u) == 0x7f800000u ? 1u : 0u;
+    }
+    return bad == 0;
   }
   if (!labels) return false;
   for (int32_t i = 0; i < n; i++)
@@ -1714,7 +1746,7 @@ static int32_t mlp_loss_grad(fr_context *c, const float *x, const int32_t *label
     return FR_E_INVALID_ARG;
   HIPCHK(hipSetDevice(c->device));
   MlpScratch s;
-  int32_t rc = mlp_alloc(s, n, 1, costs != nullptr);
+  int32_t rc = mlp_alloc(c, s, n, n, 0, costs != nullptr);
   if (rc) return rc;
   HIPCHK(hipMemcpyAsync(s.x, x, sizeof(float) * MLP_IN * n, hipMemcpyHostToDevice, c->cs));
   if (costs)
@@ -1722,9 +1754,7 @@ static int32_t mlp_loss_grad(fr_context *c, const float *x, const int32_t *label
   else
     HIPCHK(hipMemcpyAsync(s.labels, labels, sizeof(int32_t) * n, hipMemcpyHostToDevice, c->cs));
   const float *dc = costs ? s.costs : nullptr;
-  if ((rc = mlp_fwd_bwd(c, s.x, s.labels, dc, n, s, true))) return rc;
-  hipLaunchKernelGGL(k_mlp_loss, dim3(1), dim3(256), 0, c->cs, (const float *)s.probs,
-                     (const int32_t *)s.labels, dc, n, s.loss);
+  if ((rc = mlp_gradient(c, s.x, s.labels, dc, n, s, s.loss))) return rc;
   if (loss) HIPCHK(hipMemcpyAsync(loss, s.loss, sizeof(float), hipMemcpyDeviceToHost, c->cs));
   if (grad)
     HIPCHK(hipMemcpyAsync(grad, c->d.mlp_g, sizeof(float) * MLP_NPARAMS, hipMemcpyDeviceToHost, c->cs));
@@ -1756,7 +1786,7 @@ static int32_t mlp_train(fr_context *c, const float *x, const int32_t *labels, c
   hipStream_t st = c->cs;
   batch = std::min(batch, n);
   MlpScratch s;
-  int32_t rc = mlp_alloc(s, n, batch, costs != nullptr);
+  int32_t rc = mlp_alloc(c, s, n, batch, batch, costs != nullptr);
   if (rc) return rc;
   HIPCHK(hipMemcpyAsync(s.x, x, sizeof(float) * MLP_IN * n, hipMemcpyHostToDevice, st));
   if (costs)
@@ -1776,14 +1806,14 @@ static int32_t mlp_train(fr_context *c, const float *x, const int32_t *labels, c
       hipLaunchKernelGGL(k_gather_rows, dim3((batch * MLP_IN + 255) / 256), dim3(256), 0, st,
                          (const float *)s.x, (const int32_t *)s.labels, dc, (const int32_t *)s.idx,
                          batch, s.xb, s.lb, s.cb);
-      if ((rc = mlp_fwd_bwd(c, s.xb, s.lb, dcb, batch, s, true))) return rc;
+      if ((rc = mlp_gradient(c, s.xb, s.lb, dcb, batch, s, nullptr))) return rc;
       hipLaunchKernelGGL(k_adam, dim3((MLP_NPARAMS + 255) / 256), dim3(256), 0, st, c->d.mlp,
                          (const float *)c->d.mlp_g, c->d.mlp_m, c->d.mlp_v, lr, 0.9f, 0.999f, 1e-8f,
                          ++t);
       HIPCHK(hipStreamSynchronize(st));  // the host batch indices are reused
     }
     if (epoch_loss) {
-      if ((rc = mlp_fwd_bwd(c, s.x, s.labels, dc, n, s, false))) return rc;
+      if ((rc = mlp_forward(c, s.x, n, s))) return rc;
       hipLaunchKernelGGL(k_mlp_loss, dim3(1), dim3(256), 0, st, (const float *)s.probs,
                          (const int32_t *)s.labels, dc, n, s.loss);
       HIPCHK(hipMemcpyAsync(&epoch_loss[ep], s.loss, sizeof(float), hipMemcpyDeviceToHost, st));

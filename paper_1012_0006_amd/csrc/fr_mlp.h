@@ -89,11 +89,9 @@ __global__ void __launch_bounds__(256) k_features(KArgs A, const int64_t *acc, f
 }
 
 // Forward pass: MLP_SAMPLES_PER_BLOCK samples per block, one thread per
-// (sample, hidden unit).  Writes the class probabilities and, when act is
-// given, the activations a1, h1, a2, h2 ([n][64] each, in that order) for
-// the backward pass.
+// (sample, hidden unit).  Writes the class probabilities.
 __global__ void __launch_bounds__(1024) k_mlp_forward(const float *prm, const float *x, int32_t n,
-                                                      float *probs, float *act) {
+                                                      float *probs) {
   __shared__ float s_x[MLP_SAMPLES_PER_BLOCK][MLP_IN];
   __shared__ float s_h1[MLP_SAMPLES_PER_BLOCK][MLP_H];
   __shared__ float s_h2[MLP_SAMPLES_PER_BLOCK][MLP_H];
@@ -129,91 +127,213 @@ __global__ void __launch_bounds__(1024) k_mlp_forward(const float *prm, const fl
     }
     for (int c = 0; c < MLP_OUT; c++) probs[(int64_t)s * MLP_OUT + c] = e[c] / sum;
   }
-  if (ok && act) {
-    const int64_t base = (int64_t)s * MLP_H + j, stride = (int64_t)n * MLP_H;
-    act[base] = a1;
-    act[stride + base] = h1;
-    act[2 * stride + base] = a2;
-    act[3 * stride + base] = h2;
-  }
 }
 
-// Backward through the activations of each sample, for the mean softmax
-// cross-entropy (labels): dz = (p - onehot) / n; or, with per-class costs
-// [n][5], for the mean expected cost sum_c p_c cost_c: dz_j = p_j (cost_j -
-// sum_c p_c cost_c) / n.  Then da2 = (dz W3^T) * [a2 > 0], da1 = (da2 W2^T) *
-// [a1 > 0].  dact = dz [n][5], da2 [n][64], da1 [n][64].
-__global__ void __launch_bounds__(1024) k_mlp_backward(const float *prm, const float *probs,
-                                                       const int32_t *labels, const float *costs,
-                                                       int32_t n, const float *act, float *dact) {
-  __shared__ float s_dz[MLP_SAMPLES_PER_BLOCK][MLP_OUT];
-  __shared__ float s_da2[MLP_SAMPLES_PER_BLOCK][MLP_H];
-  const int ls = threadIdx.x / MLP_H, j = threadIdx.x % MLP_H;
-  const int s = blockIdx.x * MLP_SAMPLES_PER_BLOCK + ls;
-  const bool ok = s < n;
-  const int64_t stride = (int64_t)n * MLP_H;
-  if (j < MLP_OUT) {
-    float dz = 0.f;
-    if (ok && costs) {
-      const float *pr = probs + (int64_t)s * MLP_OUT, *cs = costs + (int64_t)s * MLP_OUT;
-      float pc = 0.f;
-      for (int c = 0; c < MLP_OUT; c++) pc = fmaf(pr[c], cs[c], pc);
-      dz = pr[j] * (cs[j] - pc) / (float)n;
-    } else if (ok) {
-      dz = (probs[(int64_t)s * MLP_OUT + j] - (labels[s] == j ? 1.f : 0.f)) / (float)n;
+// Loss and parameter gradients of MLP_TILE samples per workgroup, from the
+// features to partial sums (partial[tile][MLP_NPARAMS], lossp[tile]) without
+// storing an activation: forward, then for the mean softmax cross-entropy
+// (labels) dz = (p - onehot) / n, or, with per-class costs [n][5], for the
+// mean expected cost sum_c p_c cost_c: dz_j = p_j (cost_j - sum_c p_c cost_c)
+// / n; then da2 = (dz W3^T) * [h2 > 0], da1 = (da2 W2^T) * [h1 > 0] and
+// dW1 = x^T da1, db1 = sum da1, dW2 = h1^T da2, db2 = sum da2, dW3 = h2^T dz,
+// db3 = sum dz over the tile's samples.
+//
+// Each wave takes 16 of the 64 samples, a lane one hidden unit of all 16, so
+// a weight is read once for 16 FMAs and the activations are LDS broadcasts;
+// dW2 is a 4 x 4 tile per thread.  The sums of one thread per parameter over
+// all samples, which this replaces, were a serial chain of n loads: 3.97 ms
+// of a 4.4 ms call at n = 16,384; the tiles and their sum take 0.05 ms.  The
+// two-level sum is also the more exact one (64 + tiles / 4 + 4 terms in a row
+// instead of n).  Bound: launch latency and the LDS reads of one tile.
+#define MLP_TILE 64
+__global__ void __launch_bounds__(256) k_mlp_grad_tiles(const float *prm, const float *x,
+                                                        const int32_t *labels, const float *costs,
+                                                        int32_t n, float *partial, double *lossp) {
+  constexpr int Q = MLP_TILE / 4;        // samples per wave
+  constexpr int P2 = MLP_H + 1;          // pitch of W2: rows and columns free of bank conflicts
+  __shared__ float s_w1[MLP_IN * MLP_H], s_w2[MLP_H * P2], s_w3[MLP_H * MLP_OUT];
+  __shared__ float s_x[MLP_TILE * MLP_IN];
+  __shared__ __align__(16) float s_a[MLP_TILE * MLP_H];  // h1, later da1
+  __shared__ __align__(16) float s_b[MLP_TILE * MLP_H];  // h2, later da2
+  __shared__ float s_p[MLP_TILE * MLP_OUT], s_dz[MLP_TILE * MLP_OUT];
+  const int t = threadIdx.x, j = t & 63, s0 = (t >> 6) * Q;
+  const int64_t base = (int64_t)blockIdx.x * MLP_TILE;
+  const int m = (int)min((int64_t)MLP_TILE, n - base);  // samples of this tile
+  float *out = partial + (int64_t)blockIdx.x * MLP_NPARAMS;
+  for (int i = t; i < MLP_IN * MLP_H; i += 256) s_w1[i] = prm[MLP_W1 + i];
+  for (int i = t; i < MLP_H * MLP_H; i += 256) s_w2[(i / MLP_H) * P2 + i % MLP_H] = prm[MLP_W2 + i];
+  for (int i = t; i < MLP_H * MLP_OUT; i += 256) s_w3[i] = prm[MLP_W3 + i];
+  for (int i = t; i < MLP_TILE * MLP_IN; i += 256)
+    s_x[i] = i < m * MLP_IN ? x[base * MLP_IN + i] : 0.f;
+  const float b1 = prm[MLP_B1 + j], b2 = prm[MLP_B2 + j];
+  __syncthreads();
+  float v[Q];
+  // layer 1
+#pragma unroll
+  for (int q = 0; q < Q; q++) v[q] = b1;
+  for (int i = 0; i < MLP_IN; i++) {
+    const float w = s_w1[i * MLP_H + j];
+#pragma unroll
+    for (int q = 0; q < Q; q++) v[q] = fmaf(s_x[(s0 + q) * MLP_IN + i], w, v[q]);
+  }
+#pragma unroll
+  for (int q = 0; q < Q; q++) s_a[(s0 + q) * MLP_H + j] = v[q] > 0.f ? v[q] : 0.f;
+  __syncthreads();
+  // layer 2
+#pragma unroll
+  for (int q = 0; q < Q; q++) v[q] = b2;
+  for (int i = 0; i < MLP_H; i += 4) {
+    const float w0 = s_w2[i * P2 + j], w1 = s_w2[(i + 1) * P2 + j], w2 = s_w2[(i + 2) * P2 + j],
+                w3 = s_w2[(i + 3) * P2 + j];
+#pragma unroll
+    for (int q = 0; q < Q; q++) {
+      const float4 h = *reinterpret_cast<const float4 *>(&s_a[(s0 + q) * MLP_H + i]);
+      v[q] = fmaf(h.w, w3, fmaf(h.z, w2, fmaf(h.y, w1, fmaf(h.x, w0, v[q]))));
     }
-    s_dz[ls][j] = dz;
-    if (ok) dact[(int64_t)s * MLP_OUT + j] = dz;
+  }
+#pragma unroll
+  for (int q = 0; q < Q; q++) s_b[(s0 + q) * MLP_H + j] = v[q] > 0.f ? v[q] : 0.f;
+  __syncthreads();
+  // logits
+  for (int i = t; i < MLP_TILE * MLP_OUT; i += 256) {
+    const int s = i / MLP_OUT, c = i % MLP_OUT;
+    float z = prm[MLP_B3 + c];
+    for (int k = 0; k < MLP_H; k++) z = fmaf(s_b[s * MLP_H + k], s_w3[k * MLP_OUT + c], z);
+    s_p[i] = z;
   }
   __syncthreads();
-  float dh2 = 0.f;
-  for (int c = 0; c < MLP_OUT; c++) dh2 = fmaf(s_dz[ls][c], prm[MLP_W3 + j * MLP_OUT + c], dh2);
-  const float a2 = ok ? act[2 * stride + (int64_t)s * MLP_H + j] : 0.f;
-  const float da2 = a2 > 0.f ? dh2 : 0.f;
-  s_da2[ls][j] = da2;
-  __syncthreads();
-  float dh1 = 0.f;
-  for (int k2 = 0; k2 < MLP_H; k2++) dh1 = fmaf(s_da2[ls][k2], prm[MLP_W2 + j * MLP_H + k2], dh1);
-  const float a1 = ok ? act[(int64_t)s * MLP_H + j] : 0.f;
-  const float da1 = a1 > 0.f ? dh1 : 0.f;
-  if (ok) {
-    const int64_t o = (int64_t)n * MLP_OUT;
-    dact[o + (int64_t)s * MLP_H + j] = da2;
-    dact[o + stride + (int64_t)s * MLP_H + j] = da1;
+  // softmax, loss and dz, one lane of the first wave per sample
+  if (t < MLP_TILE) {
+    const int64_t g = base + t;
+    float *p = s_p + t * MLP_OUT, *dz = s_dz + t * MLP_OUT;
+    float zm = p[0], e[MLP_OUT], sum = 0.f;
+    for (int c = 1; c < MLP_OUT; c++) zm = fmaxf(zm, p[c]);
+    for (int c = 0; c < MLP_OUT; c++) {
+      e[c] = expf(p[c] - zm);
+      sum += e[c];
+    }
+    for (int c = 0; c < MLP_OUT; c++) e[c] = e[c] / sum;
+    double l = 0.0;
+    if (t >= m) {
+      for (int c = 0; c < MLP_OUT; c++) dz[c] = 0.f;
+    } else if (costs) {
+      const float *cs = costs + g * MLP_OUT;
+      float pc = 0.f;
+      for (int c = 0; c < MLP_OUT; c++) {
+        pc = fmaf(e[c], cs[c], pc);
+        l += (double)e[c] * (double)cs[c];
+      }
+      for (int c = 0; c < MLP_OUT; c++) dz[c] = e[c] * (cs[c] - pc) / (float)n;
+    } else {
+      const int y = labels[g];
+      l = -log((double)fmaxf(e[y], 1e-30f));
+      for (int c = 0; c < MLP_OUT; c++) dz[c] = (e[c] - (y == c ? 1.f : 0.f)) / (float)n;
+    }
+    for (int o = 32; o > 0; o >>= 1) l += __shfl_xor(l, o);
+    if (t == 0) lossp[blockIdx.x] = l;
   }
+  __syncthreads();
+  // da2 (in v until dW3 has read h2), dW3, db3
+  float w3r[MLP_OUT];
+  for (int c = 0; c < MLP_OUT; c++) w3r[c] = s_w3[j * MLP_OUT + c];
+#pragma unroll
+  for (int q = 0; q < Q; q++) {
+    float d = 0.f;
+    for (int c = 0; c < MLP_OUT; c++) d = fmaf(s_dz[(s0 + q) * MLP_OUT + c], w3r[c], d);
+    v[q] = s_b[(s0 + q) * MLP_H + j] > 0.f ? d : 0.f;
+  }
+  for (int i = t; i < MLP_H * MLP_OUT + MLP_OUT; i += 256) {
+    const int k = i / MLP_OUT, c = i % MLP_OUT;  // row MLP_H: the bias
+    float g = 0.f;
+    for (int s = 0; s < m; s++) {
+      const float d = s_dz[s * MLP_OUT + c];
+      g = k < MLP_H ? fmaf(s_b[s * MLP_H + k], d, g) : g + d;
+    }
+    out[MLP_W3 + i] = g;  // b3 follows W3
+  }
+  static_assert(MLP_B3 == MLP_W3 + MLP_H * MLP_OUT, "b3 follows W3");
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < Q; q++) s_b[(s0 + q) * MLP_H + j] = v[q];
+  __syncthreads();
+  // dW2 (4 x 4 per thread), db2
+  {
+    const int i0 = (t >> 4) * 4, j0 = (t & 15) * 4;
+    float g[4][4] = {};
+    for (int s = 0; s < m; s++) {
+      const float4 a = *reinterpret_cast<const float4 *>(&s_a[s * MLP_H + i0]);
+      const float4 b = *reinterpret_cast<const float4 *>(&s_b[s * MLP_H + j0]);
+      const float av[4] = {a.x, a.y, a.z, a.w}, bv[4] = {b.x, b.y, b.z, b.w};
+#pragma unroll
+      for (int r = 0; r < 4; r++)
+#pragma unroll
+        for (int c = 0; c < 4; c++) g[r][c] = fmaf(av[r], bv[c], g[r][c]);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; r++)
+#pragma unroll
+      for (int c = 0; c < 4; c++) out[MLP_W2 + (i0 + r) * MLP_H + j0 + c] = g[r][c];
+  }
+  if (t < MLP_H) {
+    float g = 0.f;
+    for (int s = 0; s < m; s++) g += s_b[s * MLP_H + t];
+    out[MLP_B2 + t] = g;
+  }
+  // da1 (in v until dW2 has read h1)
+#pragma unroll
+  for (int q = 0; q < Q; q++) v[q] = 0.f;
+  for (int k = 0; k < MLP_H; k += 4) {
+    const float w0 = s_w2[j * P2 + k], w1 = s_w2[j * P2 + k + 1], w2 = s_w2[j * P2 + k + 2],
+                w3 = s_w2[j * P2 + k + 3];
+#pragma unroll
+    for (int q = 0; q < Q; q++) {
+      const float4 d = *reinterpret_cast<const float4 *>(&s_b[(s0 + q) * MLP_H + k]);
+      v[q] = fmaf(d.w, w3, fmaf(d.z, w2, fmaf(d.y, w1, fmaf(d.x, w0, v[q]))));
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < Q; q++) {
+    float &h = s_a[(s0 + q) * MLP_H + j];
+    h = h > 0.f ? v[q] : 0.f;
+  }
+  __syncthreads();
+  // dW1, db1
+  for (int i = t; i < MLP_IN * MLP_H + MLP_H; i += 256) {
+    const int k = i / MLP_H, c = i % MLP_H;  // row MLP_IN: the bias
+    float g = 0.f;
+    for (int s = 0; s < m; s++) {
+      const float d = s_a[s * MLP_H + c];
+      g = k < MLP_IN ? fmaf(s_x[s * MLP_IN + k], d, g) : g + d;
+    }
+    out[MLP_W1 + i] = g;  // b1 follows W1
+  }
+  static_assert(MLP_B1 == MLP_W1 + MLP_IN * MLP_H, "b1 follows W1");
 }
 
-// Parameter gradients, one thread per parameter, summing over the samples in
-// index order (deterministic): dW1 = x^T da1, db1 = sum da1, dW2 = h1^T da2,
-// db2 = sum da2, dW3 = h2^T dz, db3 = sum dz.
-__global__ void __launch_bounds__(256) k_mlp_grad(const float *x, const float *act,
-                                                  const float *dact, int32_t n, float *grad) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= MLP_NPARAMS) return;
-  const int64_t stride = (int64_t)n * MLP_H;
-  const float *dz = dact, *da2 = dact + (int64_t)n * MLP_OUT, *da1 = da2 + stride;
-  const float *h1 = act + stride, *h2 = act + 3 * stride;
+// grad = sum of the tiles' partial gradients, loss = their mean loss, in a
+// fixed order: 64 parameters per workgroup, a quarter of the tiles per wave.
+__global__ void __launch_bounds__(256) k_mlp_grad_sum(const float *partial, const double *lossp,
+                                                      int32_t tiles, int32_t n, float *grad,
+                                                      float *loss) {
+  __shared__ float s_g[4][64];
+  const int seg = threadIdx.x >> 6, j = threadIdx.x & 63;
+  const int p = blockIdx.x * 64 + j;
+  const int lo = (int)((int64_t)tiles * seg / 4), hi = (int)((int64_t)tiles * (seg + 1) / 4);
   float g = 0.f;
-  if (t < MLP_B1) {
-    const int i = t / MLP_H, j = t % MLP_H;
-    for (int s = 0; s < n; s++) g = fmaf(x[(int64_t)s * MLP_IN + i], da1[(int64_t)s * MLP_H + j], g);
-  } else if (t < MLP_W2) {
-    const int j = t - MLP_B1;
-    for (int s = 0; s < n; s++) g += da1[(int64_t)s * MLP_H + j];
-  } else if (t < MLP_B2) {
-    const int i = (t - MLP_W2) / MLP_H, j = (t - MLP_W2) % MLP_H;
-    for (int s = 0; s < n; s++) g = fmaf(h1[(int64_t)s * MLP_H + i], da2[(int64_t)s * MLP_H + j], g);
-  } else if (t < MLP_W3) {
-    const int j = t - MLP_B2;
-    for (int s = 0; s < n; s++) g += da2[(int64_t)s * MLP_H + j];
-  } else if (t < MLP_B3) {
-    const int i = (t - MLP_W3) / MLP_OUT, c = (t - MLP_W3) % MLP_OUT;
-    for (int s = 0; s < n; s++) g = fmaf(h2[(int64_t)s * MLP_H + i], dz[(int64_t)s * MLP_OUT + c], g);
-  } else {
-    const int c = t - MLP_B3;
-    for (int s = 0; s < n; s++) g += dz[(int64_t)s * MLP_OUT + c];
+  if (p < MLP_NPARAMS) {
+#pragma unroll 8
+    for (int i = lo; i < hi; i++) g += partial[(int64_t)i * MLP_NPARAMS + p];
   }
-  grad[t] = g;
+  s_g[seg][j] = g;
+  __syncthreads();
+  if (seg == 0 && p < MLP_NPARAMS) grad[p] = ((s_g[0][j] + s_g[1][j]) + s_g[2][j]) + s_g[3][j];
+  if (loss && blockIdx.x == 0 && seg == 1) {
+    double l = 0.0;
+    for (int i = j; i < tiles; i += 64) l += lossp[i];
+    for (int o = 32; o > 0; o >>= 1) l += __shfl_xor(l, o);
+    if (j == 0) *loss = (float)(l / (n > 0 ? n : 1));
+  }
 }
 
 // mean cross-entropy of n samples (labels), or their mean expected cost

@@ -53,12 +53,12 @@ struct DevBufs {
   int64_t mbccap = 0;
   int32_t *fmg = nullptr, *fmq = nullptr;  // 2-way FM: per-vertex gains, queue positions (lazy)
   int64_t fmcap = 0;
-  // multi-try FM (lazy): per vertex touched stamps, targets, heap slots, heap
-  // overflow [2n], move log [n] x 2; todo keys per arena slot x 2; per block
+  // multi-try FM (lazy): per vertex touched stamps, targets, queue slots,
+  // queue entries beyond LDS [n] x 2, move log [n] x 2; todo keys per arena slot x 2; per block
   // weights and changed flags
   int32_t *mtt = nullptr, *mtb = nullptr, *mtq = nullptr, *mth = nullptr, *mtv = nullptr,
           *mtf = nullptr;
-  unsigned long long *mtk = nullptr, *mtk2 = nullptr;
+  unsigned long long *mtk = nullptr, *mtk2 = nullptr, *mtr = nullptr;
   int64_t *mtw = nullptr;
   uint8_t *mtchg = nullptr;
   int64_t mtncap = 0, mtscap = 0, mtkcap = 0;
@@ -158,6 +158,8 @@ static void free_vertex_arc(DevBufs &d) {
     dfree(*pp);
     *pp = nullptr;
   }
+  dfree(d.mtr);
+  d.mtr = nullptr;
   dfree(d.mtk);
   dfree(d.mtk2);
   d.mtk = d.mtk2 = nullptr;
@@ -582,6 +584,7 @@ static KArgs call_args(fr_context *c, const DevBufs &d, const fr_graph *g, int32
     A.mtt = d.mtt;
     A.mtb = d.mtb;
     A.mtq = d.mtq;
+    A.mtr = d.mtr;
     A.mth = d.mth;
     A.mtv = d.mtv;
     A.mtf = d.mtf;
@@ -1042,12 +1045,15 @@ static int32_t ensure_mb(fr_context *c, const fr_params *p) {
         dfree(*pp);
         *pp = nullptr;
       }
+      dfree(d.mtr);
+      d.mtr = nullptr;
       d.mtncap = 0;
       if (dalloc(&d.mtt, d.ncap) != hipSuccess || dalloc(&d.mtb, d.ncap) != hipSuccess ||
-          dalloc(&d.mtq, d.ncap) != hipSuccess || dalloc(&d.mth, 2 * d.ncap) != hipSuccess ||
-          dalloc(&d.mtv, d.ncap) != hipSuccess || dalloc(&d.mtf, d.ncap) != hipSuccess)
+          dalloc(&d.mtq, d.ncap) != hipSuccess || dalloc(&d.mth, d.ncap) != hipSuccess ||
+          dalloc(&d.mtv, d.ncap) != hipSuccess || dalloc(&d.mtf, d.ncap) != hipSuccess ||
+          dalloc(&d.mtr, d.ncap) != hipSuccess)
         return FR_E_OOM;
-      // touched stamps start below every stamp in use, heap slots at -1
+      // touched stamps start below every stamp in use, queue slots at -1
       HIPCHK(hipMemset(d.mtt, 0, sizeof(int32_t) * (size_t)d.ncap));
       HIPCHK(hipMemset(d.mtq, 0xff, sizeof(int32_t) * (size_t)d.ncap));
       d.mtncap = d.ncap;

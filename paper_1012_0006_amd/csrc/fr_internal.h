@@ -163,13 +163,13 @@ struct KArgs {
   // multi-try FM after the round (0 = off): stopping-rule alpha, key seed,
   // beta = floor(ln n 2^16), touched stamp of the round's first pair minus 1;
   // block weights [k], todo keys and their sort buffer (arena slots),
-  // per-vertex touched stamps, targets and heap slots (-1 none), heap slots
-  // beyond LDS [2n], move log of a search [n] x 2, changed blocks [k]
+  // per-vertex touched stamps, targets and queue slots (-1 none), the queue's
+  // ranks and vertices beyond LDS [n] each, move log of a search [n] x 2, changed blocks [k]
   int32_t mt_alpha, mt_seed;
   int64_t mt_beta;
   int32_t mt_stamp0;
   int64_t *mtw;
-  unsigned long long *mtk, *mtk2;
+  unsigned long long *mtk, *mtk2, *mtr;
   int32_t *mtt, *mtb, *mtq, *mth, *mtv, *mtf;
   uint8_t *mtchg;
   // terminals of the corridor network: 0 border pinned by infinite arcs,

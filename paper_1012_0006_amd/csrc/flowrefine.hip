@@ -888,7 +888,7 @@ static int32_t enqueue_round(fr_context *c, KArgs A, bool use_mlp, hipStream_t s
     hipLaunchKernelGGL(k_mt_weights, dim3(sblocks), dim3(256), 0, st, A);
     hipLaunchKernelGGL(k_mt_todo, dim3(sblocks), dim3(256), 0, st, A);
     hipLaunchKernelGGL(k_mt_sort, dim3(A.P / A.W), dim3(MT_SORT_TPB), 0, st, A);
-    hipLaunchKernelGGL(k_mt, dim3(1), dim3(WAVE), 0, st, A);
+    hipLaunchKernelGGL(k_mt, dim3(1), dim3(MT_TPB), 0, st, A);
   }
   HIPCHK(hipGetLastError());
   c->timed_iters = timed ? (fused ? 1 : launches) : 0;

@@ -56,7 +56,7 @@ __device__ __forceinline__ int64_t row_index(const u64 *L, int32_t nr, int32_t i
   return (int64_t)ROW_WORDS * ((int64_t)nr + ovf) + (slot - ROW_SLOTS);
 }
 
-// ---- lane groups (G = 2, 4 or 8 consecutive lanes) on the DPP crossbar: a
+// ---- lane groups (G = 2, 4 or 8 consecutive lanes, 16 for reductions) on the DPP crossbar: a
 //      step costs a few cycles where a bpermute through LDS costs tens.  All
 //      64 lanes of the wave take part.
 template <int CTRL>
@@ -66,6 +66,7 @@ __device__ __forceinline__ int32_t dpp(int32_t x) {
 #define DPP_XOR1 0xB1        // quad_perm [1,0,3,2]
 #define DPP_XOR2 0x4E        // quad_perm [2,3,0,1]
 #define DPP_HALF_MIRROR 0x141  // lane i of 8 reads lane 7 - i
+#define DPP_MIRROR 0x140     // lane i of 16 reads lane 15 - i
 #define DPP_SHR(n) (0x110 | (n))
 
 // value of the group's first lane
@@ -83,6 +84,7 @@ __device__ __forceinline__ int32_t group_reduce(int32_t x, Op &&op) {
   x = op(x, dpp<DPP_XOR1>(x));
   if (G >= 4) x = op(x, dpp<DPP_XOR2>(x));
   if (G >= 8) x = op(x, dpp<DPP_HALF_MIRROR>(x));
+  if (G >= 16) x = op(x, dpp<DPP_MIRROR>(x));
   return x;
 }
 

@@ -1,6 +1,7 @@
 """The queue of the multi-try searches where its handling changes: more
-entries than one scan takes, than its local store and than its group bounds
-hold; and gains of vertices whose arcs no longer fit one lane's registers."""
+entries than a request answers, than one scan takes (1,024), than its local
+store (2,048) and than its group bounds (65,536) hold; and gains of vertices
+whose arcs no longer fit a lane group's registers (32)."""
 import numpy as np
 import pytest
 
@@ -22,7 +23,7 @@ def _params(seed):
                 eps_ppm=1_000_000, mt_alpha=1_000_000, mt_seed=seed)
 
 
-@pytest.mark.parametrize("leaves", [255, 257, 3071, 3073, 65536, 70000])
+@pytest.mark.parametrize("leaves", [15, 63, 64, 1022, 1023, 1024, 2046, 2047, 2048, 65535, 65536, 70000])
 def test_queue_of_a_star(gpu_lib, ctx, leaves):
     """A hub whose leaves are in three other blocks: its search queues the
     leaves together and pops them all (no stopping rule applies)."""

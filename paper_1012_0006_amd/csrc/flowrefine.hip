@@ -331,7 +331,8 @@ extern "C" int32_t fr_create(int32_t device, void *hip_stream, fr_context **out)
   c->num_cus = prop.multiProcessorCount;
   c->lds_bytes = std::max<size_t>(65536, prop.sharedMemPerBlock);
   for (const void *fn : {(const void *)k_flow<256>, (const void *)k_flow<512>,
-                         (const void *)k_flow<1024>})
+                         (const void *)k_flow<1024>, (const void *)k_corr<256>,
+                         (const void *)k_corr<512>, (const void *)k_corr<1024>})
     if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)c->lds_bytes - 2048) != hipSuccess) {
       (void)hipGetLastError();
@@ -754,6 +755,24 @@ static size_t flow_lds_bytes(const fr_context *c, int32_t blocks, int tpb) {
   return std::max(fixed, share > other ? share - other : 0);
 }
 
+// Dynamic LDS of the corridor kernel for workgroups of tpb threads, and the
+// words of its bitmap: as many as the graph has vertices for, or none where
+// they don't fit or would leave fewer workgroups on a CU than the launch has
+// for it (a bit per vertex: up to about 1.1 million vertices with one
+// workgroup per CU).
+static size_t corr_lds_bytes(const fr_context *c, KArgs &A, int32_t blocks, int tpb) {
+  const size_t off = tpb == 256   ? offsetof(SolveShared<256>, u)
+                     : tpb == 512 ? offsetof(SolveShared<512>, u)
+                                  : offsetof(SolveShared<1024>, u);
+  const size_t fixed = solve_shared_bytes(tpb), hist = sizeof(SolveShared<1024>::u.hist);
+  const size_t bits = ((size_t)A.n + 63) / 64 * 8, lists = 16 * CORR_LIST;
+  const size_t limit = flow_lds_bytes(c, blocks, tpb);
+  const bool fits = off + hist + bits <= limit;
+  const size_t bytes = std::min(limit, off + hist + bits + lists) & ~(size_t)15;
+  A.corr_words = fits ? (int64_t)((bytes - off - hist) / 4) : 0;
+  return std::max(fixed, fits ? bytes : (size_t)0);
+}
+
 static void set_row_limits(KArgs &A, size_t bytes, int tpb) {
   const size_t off = tpb == 256   ? offsetof(SolveShared<256>, u)
                      : tpb == 512 ? offsetof(SolveShared<512>, u)
@@ -779,6 +798,7 @@ static int32_t enqueue_round(fr_context *c, KArgs A, bool use_mlp, hipStream_t s
   const bool fused = c->fused && A.mb_reps == 0 && A.W == 1;
   const size_t flow_lds = flow_lds_bytes(c, blocks, tpb);
   set_row_limits(A, flow_lds, tpb);
+  const size_t corr_lds = corr_lds_bytes(c, A, blocks, tpb);
   if (fused) A.row_nr = -1;  // k_round builds and solves the CSR form
   // no network of the round can need the CSR form (every vertex and arc fits
   // a row, and so do all rows the array): its kernels stay away
@@ -861,7 +881,7 @@ static int32_t enqueue_round(fr_context *c, KArgs A, bool use_mlp, hipStream_t s
     if (timed) HIPCHK(hipEventRecord(ev[0], st));
     hipLaunchKernelGGL(k_iter_begin, dim3(1), dim3(1024), 0, st, A, it);
     hipLaunchKernelGGL(k_bnd, dim3(c->g_bnd), dim3(256), 0, st, A, it);
-    hipLaunchKernelGGL(corr, dim3(blocks), dim3(tpb), 0, st, A, it);
+    hipLaunchKernelGGL(corr, dim3(blocks), dim3(tpb), corr_lds, st, A, it);
     hipLaunchKernelGGL(k_iter_mid, dim3(1), dim3(1024), 0, st, A, it);
     if (timed) HIPCHK(hipEventRecord(ev[1], st));
     hipLaunchKernelGGL(k_net_count, dim3(sblocks), dim3(256), 0, st, A, it);

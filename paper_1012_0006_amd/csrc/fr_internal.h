@@ -199,6 +199,8 @@ struct KArgs {
   // row networks: bytes of the flow kernel's LDS they may use, and the
   // largest corridor whose bitmaps and lists fit them
   int64_t flow_lds, row_nr;
+  // words of the corridor kernel's bitmap of reached vertices (0 none)
+  int64_t corr_words;
   int8_t *side_out;
 };
 

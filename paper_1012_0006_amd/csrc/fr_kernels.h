@@ -132,6 +132,7 @@ __device__ void block_sums(int64_t (&v)[N], int64_t *lds) {
 // frontier list live in LDS, the rest in the pair's global list.
 #define FR_BM_WORDS 4096
 #define FR_LDS_LIST 2048
+#define CORR_LIST 2048   // vertices of a corridor level with an entry in LDS
 
 #include "fr_rows.h"
 
@@ -594,6 +595,8 @@ struct SolveShared {
   int64_t red[16 * 8];            // block reductions
   int64_t scan[TPB / 64 + 1];
   int64_t W[2], U[2];             // BFS: taken weight and bound per side
+  unsigned long long lw[3][2];    // BFS: weight and vertices of a level per side
+  int32_t lc[3][2];
   int64_t rarcs, rcap, rcin;      // corridor arcs, capacity sum, old a-b weight inside
   fr_solve rec;                   // record of the current solve
   unsigned long long work[W_COUNT];
@@ -920,24 +923,6 @@ __device__ __forceinline__ void for_groups(int32_t N, F &&f) {
     const int item = base + (gid - wf);
     f(item, item < N, gl);
   }
-}
-
-// Lanes per item of a corridor BFS level: GTF while the level fits one pass
-// of the workgroup, else 2, else 1 -- every extra pass would pay the level's
-// chain of dependent loads again; each item keeps 8 arcs in flight at any
-// width.  f(Lanes<G>) runs the level; results do not depend on G.  (The flow
-// phases' searches keep GTF lanes: their levels are short, and one
-// instantiation keeps that kernel within its registers.)
-template <int G>
-struct Lanes {
-  static constexpr int g = G, k = 8 / G;
-};
-
-template <typename F>
-__device__ __forceinline__ void by_width(int32_t cnt, F &&f) {
-  if ((int64_t)cnt * GTF <= (int64_t)blockDim.x) f(Lanes<GTF>{});
-  else if ((int64_t)cnt * 2 <= (int64_t)blockDim.x) f(Lanes<2>{});
-  else f(Lanes<1>{});
 }
 
 // Sets the bitmap words of vertices 0..nr-1 to the ballot of pred(i) (one
@@ -1415,9 +1400,181 @@ __device__ __forceinline__ int32_t next_pair(const KArgs &A, int32_t *queue,
 // ---- bounded BFS corridor (Sec. 4.1): level-synchronous on both sides from
 //      the boundary; a level that crosses the side's area bound is cut in
 //      ascending vertex id.  Taken vertices get local ids (lg, vmap).
-template <int TPB>
-__device__ __forceinline__ void corr_pair(const KArgs &A, int32_t S, int32_t p, SolveShared<TPB> &sh,
-                          PairState &st) {
+//
+//      Wide levels are bound by the accesses of one CU to single cache lines,
+//      narrow ones by the chain of dependent loads of a level.  So a vertex's
+//      arcs are read by 8 lanes together, and what has been reached is a
+//      bitmap over the vertices in LDS: an arc costs a bit test, and only the
+//      first arc to reach a vertex reads its block and weight.  (An arc from
+//      one side never is the first to reach a vertex of the other: its ends
+//      would be boundary vertices, which are reached from the start.)  Graphs
+//      whose bitmap doesn't fit use the marks in memory.  Measured, one
+//      launch: 32 pairs' corridors in a sweep of narrow ones 85 -> 44 us, in
+//      a sweep of wide ones 434 -> 264 us; before, an arc read its head's
+//      block, mark and weight, and marks were claimed by atomics in memory.
+
+// Vertices reached: a bit each in LDS, or the entry's marks.  After a narrow
+// level the first `cap` vertices of the next also have an entry in LDS, made
+// when they are reached: first arc, degree and side (cur and nxt: this level's
+// and the next's), so that a narrow level's chain of loads is its arcs and the
+// heads' data.
+struct Reached {
+  uint32_t *bm;
+  int32_t *mk;
+  int32_t S;
+  int32_t cap, have;  // have: cap when this level has its entries, else 0
+  int2 *cur, *nxt;
+};
+__device__ __forceinline__ int2 reached_entry(int32_t e0, int32_t e1, bool side) {
+  return make_int2(e0, ((e1 - e0) << 1) | (side ? 1 : 0));  // (degrees are below 2^30)
+}
+
+// Expands the level `cur` (cnt vertices) on the sides that go on, and lets
+// its vertices join the corridor on the way when `join` is set (sides with
+// mode 1).  8 lanes per vertex, JI vertices per group at once.  Adds the
+// reached vertices' weights and numbers per side to the sums in `slot`, and
+// the vertices and arcs expanded to work.
+template <int TPB, bool LB, int JI>
+__device__ __forceinline__ void corr_level(const KArgs &A, const PairView &V, const Reached R,
+                                           const int32_t *cur, int32_t *nxt, int32_t cnt,
+                                           int32_t *ncnt, int32_t *vm, bool join,
+                                           SolveShared<TPB> &sh, int slot,
+                                           int64_t (&work)[2]) {
+  constexpr int G = 8, NG = TPB / G, KW = 2;
+  const int lane = lane64(), gl = lane & (G - 1), gid = (int)threadIdx.x / G;
+  const int32_t va = V.a, vb = V.b;
+  const bool on0 = uni(sh.state[0]) != 0, on1 = uni(sh.state[1]) != 0;
+  const bool take0 = join && uni(sh.mode[0]) == 1, take1 = join && uni(sh.mode[1]) == 1;
+  int64_t wt[2] = {0, 0};
+  int32_t ct[2] = {0, 0};  // (the same in every lane)
+  for (int32_t base = 0; base < cnt; base += NG * JI) {
+    // a lane per vertex: its first arc, degree and side
+    int32_t he = 0, hd = 0;
+    {
+      const int32_t item = base + gl * NG + gid;
+      const bool valid = gl < JI && item < cnt;
+      bool take = false;
+      int32_t u = 0;
+      if (valid) {
+        u = cur[item];  // (not in the chain unless the entry is missing)
+        int2 h;
+        if (item < R.have) h = R.cur[item];
+        else h = reached_entry(A.xadj[u], A.xadj[u + 1], A.part[u] == vb);
+        const bool s = h.y & 1;
+        he = h.x;
+        hd = h.y;
+        take = s ? take1 : take0;
+        if (!(s ? on1 : on0)) {
+          hd &= 1;
+        } else {
+          work[0] += 1;
+          work[1] += hd >> 1;
+        }
+      }
+      if (join) {
+        const int pos = wave_append(&sh.nr, take);
+        if (take) {
+          put_bounded(V.lg, pos, V.nv, u, A.ctl);
+          vm[u] = pos;
+        }
+      }
+    }
+    int32_t e[JI], d[JI];
+    bool x[JI];
+    int32_t dmax = 0;
+#pragma unroll
+    for (int j = 0; j < JI; j++) {
+      const int from = (lane & ~(G - 1)) | j;
+      e[j] = __shfl(he, from);
+      d[j] = __shfl(hd, from);
+      x[j] = d[j] & 1;
+      d[j] >>= 1;
+      dmax = max(dmax, d[j]);
+    }
+    for (int32_t c0 = 0; ballot64(c0 < dmax) != 0ull; c0 += G * KW) {
+      int32_t v[JI * KW], xv[JI * KW];
+      bool got[JI * KW];
+#pragma unroll
+      for (int i = 0; i < JI * KW; i++) {
+        const int32_t c = c0 + (i % KW) * G + gl;
+        v[i] = c < d[i / KW] ? A.adjncy[e[i / KW] + c] : -1;
+      }
+      if (LB) {
+        uint32_t word[JI * KW];
+#pragma unroll
+        for (int i = 0; i < JI * KW; i++) word[i] = v[i] >= 0 ? R.bm[v[i] >> 5] : ~0u;
+#pragma unroll
+        for (int i = 0; i < JI * KW; i++) {
+          const uint32_t bit = 1u << (v[i] & 31);
+          got[i] = false;
+          if (!(word[i] & bit)) got[i] = !(atomicOr(&R.bm[v[i] >> 5], bit) & bit);
+        }
+#pragma unroll
+        for (int i = 0; i < JI * KW; i++) xv[i] = got[i] ? A.part[v[i]] : -1;
+      } else {
+        int32_t mv[JI * KW];
+#pragma unroll
+        for (int i = 0; i < JI * KW; i++) {
+          xv[i] = v[i] >= 0 ? A.part[v[i]] : -1;
+          mv[i] = v[i] >= 0 ? R.mk[v[i]] : R.S;
+        }
+#pragma unroll
+        for (int i = 0; i < JI * KW; i++) {
+          got[i] = v[i] >= 0 && xv[i] == (x[i / KW] ? vb : va) && mv[i] < R.S;
+          if (got[i]) got[i] = atomicMax(&R.mk[v[i]], R.S) < R.S;
+        }
+      }
+      int32_t w[JI * KW], f0[JI * KW], f1[JI * KW];
+#pragma unroll
+      for (int i = 0; i < JI * KW; i++) {
+        w[i] = got[i] ? A.vwgt[v[i]] : 0;
+        f0[i] = JI == 1 && got[i] ? A.xadj[v[i]] : 0;
+        f1[i] = JI == 1 && got[i] ? A.xadj[v[i] + 1] : 0;
+      }
+      u64 m[JI * KW];
+      int32_t total = 0;
+#pragma unroll
+      for (int i = 0; i < JI * KW; i++) {
+        got[i] = got[i] && xv[i] == (x[i / KW] ? vb : va);
+        m[i] = ballot64(got[i]);
+        const int32_t all = (int32_t)__popcll(m[i]),
+                      side = (int32_t)__popcll(m[i] & ballot64(x[i / KW]));
+        total += all;
+        ct[0] += all - side;
+        ct[1] += side;
+      }
+      if (total == 0) continue;
+      int32_t at = 0;
+      if (lane == 0) at = atomicAdd(ncnt, total);
+      at = uni(at);
+#pragma unroll
+      for (int i = 0; i < JI * KW; i++) {
+        if (got[i]) {
+          const int32_t pos = at + lanes_below(m[i]);
+          put_bounded(nxt, pos, V.nv, v[i], A.ctl);
+          if (JI == 1 && pos < R.cap) R.nxt[pos] = reached_entry(f0[i], f1[i], x[i / KW]);
+          if (LB) R.mk[v[i]] = R.S;
+          wt[0] += x[i / KW] ? 0 : w[i];
+          wt[1] += x[i / KW] ? w[i] : 0;
+        }
+        at += (int32_t)__popcll(m[i]);
+      }
+    }
+  }
+#pragma unroll
+  for (int s = 0; s < 2; s++) {
+    if (ct[s] == 0) continue;
+    for (int o = 32; o > 0; o >>= 1) wt[s] += __shfl_xor((long long)wt[s], o);
+    if (lane == 0) {
+      atomicAdd(&sh.lw[slot][s], (unsigned long long)wt[s]);
+      atomicAdd(&sh.lc[slot][s], ct[s]);
+    }
+  }
+}
+
+template <int TPB, bool LB>
+__device__ __forceinline__ void corr_grow(const KArgs &A, int32_t S, int32_t p, uint32_t *bm, int64_t words,
+                                          SolveShared<TPB> &sh, PairState &st) {
   const PairView V = make_view(A, p);
   const int32_t a = V.a, b = V.b;
   int32_t *mk = mark_of(A, p), *vm = vmap_of(A, p);
@@ -1439,7 +1596,19 @@ __device__ __forceinline__ void corr_pair(const KArgs &A, int32_t S, int32_t p, 
     if (st.cut0 < 0) st.cut0 = pa[PA_CUT];
     st.cut = pa[PA_CUT];
   }
-  if (threadIdx.x < W_COUNT) sh.work[threadIdx.x] = 0ull;
+  if (threadIdx.x < 2) {
+    sh.lw[0][threadIdx.x] = (unsigned long long)pa[PA_BW0 + threadIdx.x];
+    sh.lc[0][threadIdx.x] = (int32_t)pa[PA_BC0 + threadIdx.x];
+  }
+  // a level of up to two steps of the groups, one vertex each; wider ones go
+  // with 4 vertices per group and step (8 arcs in flight per lane)
+  auto narrow = [](int32_t cnt) { return cnt * 8 <= 2 * TPB; };
+  int32_t cap = 0, have = 0;  // see Reached; entries lie at bm + at, cap for each of two levels
+  const int32_t at = ((A.n + 31) / 32 + 1) & ~1;
+  if (LB) {  // what the bitmap leaves holds the levels' entries, 16 bytes for both
+    cap = (int32_t)max((int64_t)0, min((words - at) / 4, (int64_t)CORR_LIST));
+    for (int32_t i = threadIdx.x; i < (A.n + 31) / 32; i += TPB) bm[i] = 0u;
+  }
   __syncthreads();
   {
     // level 0: the pair's boundary list into this entry's list, the other
@@ -1447,14 +1616,17 @@ __device__ __forceinline__ void corr_pair(const KArgs &A, int32_t S, int32_t p, 
     // marks were set by the boundary pass)
     const int32_t *bl = A.SNK + A.voff[p0];
     const int32_t n0 = uni(sh.cnt[0]);
+    have = narrow(n0) ? cap : 0;
     for (int32_t i = threadIdx.x; i < n0; i += TPB) {
       const int32_t u = bl[i];
       V.LA[i] = u;
       if (p != p0) mk[u] = S;
+      if (LB) atomicOr(&bm[u >> 5], 1u << (u & 31));
+      if (i < have) reinterpret_cast<int2 *>(bm + at)[i] = reached_entry(A.xadj[u], A.xadj[u + 1], A.part[u] == b);
     }
     __syncthreads();
   }
-  int64_t Lw[2] = {pa[PA_BW0], pa[PA_BW1]}, Lc[2] = {pa[PA_BC0], pa[PA_BC1]};
+  int64_t work[2] = {0, 0};  // vertices and arcs expanded by this lane
   int32_t *cur = V.LA, *nxt = V.LB;
   int cc = 0;  // counter of the current list
   for (int32_t lev = 0;; lev++) {
@@ -1463,115 +1635,99 @@ __device__ __forceinline__ void corr_pair(const KArgs &A, int32_t S, int32_t p, 
       for (int s = 0; s < 2; s++) {
         sh.mode[s] = 0;
         if (!sh.state[s]) continue;
-        if (Lc[s] == 0) {
+        if (sh.lc[cc][s] == 0) {
           sh.state[s] = 0;
           continue;
         }
+        const int64_t Lw = (int64_t)sh.lw[cc][s];
         if (A.area_mode == FR_AREA_DEPTH) {
           sh.mode[s] = 1;
-          sh.W[s] += Lw[s];
+          sh.W[s] += Lw;
           if (lev >= A.depth) sh.state[s] = 0;
-        } else if (sh.W[s] + Lw[s] <= sh.U[s]) {
+        } else if (sh.W[s] + Lw <= sh.U[s]) {
           sh.mode[s] = 1;
-          sh.W[s] += Lw[s];
+          sh.W[s] += Lw;
         } else {
           sh.mode[s] = 2;  // the bound is crossed inside this level
           sh.state[s] = 0;
         }
       }
-      sh.cnt[(cc + 1) % 3] = 0;
+      const int next = (cc + 1) % 3;
+      sh.cnt[next] = 0;
+      for (int s = 0; s < 2; s++) {
+        sh.lw[next][s] = 0ull;
+        sh.lc[next][s] = 0;
+      }
       st.bfs_levels += 1;
     }
     __syncthreads();
-    for (int s = 0; s < 2; s++)
-      if (sh.mode[s] == 2) cut_level<TPB>(A, mk, s ? b : a, cur, cnt, sh.U[s] - sh.W[s], S, sh);
-    // the taken part of this level joins the corridor
-    BLOCK_WAVE_LOOP(i, cnt) {
-      bool take = false;
-      int32_t u = 0;
-      if (i < cnt) {
-        u = cur[i];
-        const int s = A.part[u] == b;
-        take = sh.mode[s] == 1 || (sh.mode[s] == 2 && mk[u] == S);
-      }
-      const int pos = wave_append(&sh.nr, take);
-      if (take) {
-        put_bounded(V.lg, pos, V.nv, u, A.ctl);
-        vm[u] = pos;
+    const bool expand = uni(sh.state[0] | sh.state[1]) != 0;
+    const bool join = expand && uni(sh.mode[0]) != 2 && uni(sh.mode[1]) != 2;
+    if (!join) {
+      for (int s = 0; s < 2; s++)
+        if (sh.mode[s] == 2) cut_level<TPB>(A, mk, s ? b : a, cur, cnt, sh.U[s] - sh.W[s], S, sh);
+      // the taken part of this level joins the corridor
+      BLOCK_WAVE_LOOP(i, cnt) {
+        bool take = false;
+        int32_t u = 0;
+        if (i < cnt) {
+          u = cur[i];
+          const int s = A.part[u] == b;
+          take = sh.mode[s] == 1 || (sh.mode[s] == 2 && mk[u] == S);
+        }
+        const int pos = wave_append(&sh.nr, take);
+        if (take) {
+          put_bounded(V.lg, pos, V.nv, u, A.ctl);
+          vm[u] = pos;
+        }
       }
     }
-    if (!sh.state[0] && !sh.state[1]) break;
-    // expand the sides that go on
-    int64_t acc2[4] = {0, 0, 0, 0};  // weight a, weight b, count a, count b
-    int32_t *ncnt = &sh.cnt[(cc + 1) % 3];
-    // GTF lanes per frontier vertex, KF arcs per lane: the neighbours'
-    // block, mark and weight are loaded together, ahead of the claims
-    by_width(cnt, [&](auto L) {
-      constexpr int GW = decltype(L)::g, KW = decltype(L)::k;
-      for_groups<GW>(cnt, [&](int item, bool valid, int gl) {
-        const int32_t u = valid ? cur[item] : 0;
-        const int32_t x = valid ? A.part[u] : -1;
-        const int32_t e0 = valid ? A.xadj[u] : 0, e1 = valid ? A.xadj[u + 1] : 0;
-        const int s = x == b;
-        const bool go = valid && sh.state[s];
-        count_work(sh, W_BFS_ITEMS, (go && gl == 0) ? 1 : 0);
-        count_work(sh, W_BFS_ARCS, (go && gl == 0) ? e1 - e0 : 0);
-        const int32_t ee = go ? e1 : e0;
-        for (int32_t c0 = e0; c0 < ee; c0 += GW * KW) {
-          int32_t v[KW], xv[KW], mv[KW], wv[KW];
-#pragma unroll
-          for (int k = 0; k < KW; k++) {
-            const int32_t e = c0 + k * GW + gl;
-            v[k] = e < ee ? A.adjncy[e] : -1;
-          }
-#pragma unroll
-          for (int k = 0; k < KW; k++) {
-            xv[k] = v[k] >= 0 ? A.part[v[k]] : -1;
-            mv[k] = v[k] >= 0 ? mk[v[k]] : S;
-            wv[k] = v[k] >= 0 ? A.vwgt[v[k]] : 0;
-          }
-#pragma unroll
-          for (int k = 0; k < KW; k++) {
-            bool claim = false;
-            if (v[k] >= 0 && xv[k] == x && mv[k] < S) claim = atomicMax(&mk[v[k]], S) < S;
-            const int pos = wave_append(ncnt, claim);
-            if (claim) {
-              put_bounded(nxt, pos, V.nv, v[k], A.ctl);
-              acc2[s] += wv[k];
-              acc2[2 + s] += 1;
-            }
-          }
-        }
-      });
-    });
-    block_sums<4>(acc2, sh.red);
-    Lw[0] = acc2[0];
-    Lw[1] = acc2[1];
-    Lc[0] = acc2[2];
-    Lc[1] = acc2[3];
+    if (!expand) break;
+    const int next = (cc + 1) % 3;
+    int32_t *ncnt = &sh.cnt[next];
+    int2 *const ent = reinterpret_cast<int2 *>(bm + at);
+    const Reached R{bm, mk, S, cap, have, ent + (lev & 1) * cap, ent + (~lev & 1) * cap};
+    if (narrow(cnt))
+      corr_level<TPB, LB, 1>(A, V, R, cur, nxt, cnt, ncnt, vm, join, sh, next, work);
+    else
+      corr_level<TPB, LB, 4>(A, V, R, cur, nxt, cnt, ncnt, vm, join, sh, next, work);
+    __syncthreads();
+    have = narrow(cnt) ? cap : 0;
     int32_t *t = cur;
     cur = nxt;
     nxt = t;
     cc = (cc + 1) % 3;
   }
   __syncthreads();
+  block_sums<2>(work, sh.red);
   if (threadIdx.x == 0) {
     st.nr = min(sh.nr, (int32_t)V.nv);
-    for (int j = 0; j < W_COUNT; j++) st.work[j] += (int64_t)sh.work[j];
+    st.work[W_BFS_ITEMS] += work[0];
+    st.work[W_BFS_ARCS] += work[1];
     st.t_corridor += wall_clock64() - t0;
     A.ps[p] = st;
   }
   __syncthreads();
 }
 
+// The bitmap lies in the union behind cut_level's histogram, `words` words.
+template <int TPB>
+__device__ __forceinline__ void corr_pair(const KArgs &A, int32_t S, int32_t p,
+                                          SolveShared<TPB> &sh, PairState &st, int64_t words) {
+  uint32_t *bm = reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(&sh.u) + sizeof(sh.u.hist));
+  if ((int64_t)A.n <= 32 * words) corr_grow<TPB, true>(A, S, p, bm, words, sh, st);
+  else corr_grow<TPB, false>(A, S, p, bm, words, sh, st);
+}
+
 template <int TPB>
 __global__ void __launch_bounds__(TPB) k_corr(KArgs A, int32_t it) {
-  __shared__ SolveShared<TPB> sh;
+  extern __shared__ __align__(16) unsigned char corr_lds[];
+  SolveShared<TPB> &sh = *reinterpret_cast<SolveShared<TPB> *>(corr_lds);
   __shared__ PairState st;
   for (;;) {
     const int32_t p = next_pair<TPB>(A, A.queue + FR_QUEUE * (it % A.max_iters), sh, 0);
     if (p < 0) break;
-    corr_pair<TPB>(A, stamp_of(A, p), p, sh, st);
+    corr_pair<TPB>(A, stamp_of(A, p), p, sh, st, A.corr_words);
   }
 }
 
@@ -2038,7 +2194,8 @@ __global__ void __launch_bounds__(TPB) k_round(KArgs A) {
     for (int32_t it = 0; it < A.max_iters; it++) {
       bnd_union(A, [&](auto &&f) { pair_items(p, nu, f); });
       __syncthreads();
-      corr_pair<TPB>(A, stamp_of(A, p), p, sh, st);
+      corr_pair<TPB>(A, stamp_of(A, p), p, sh, st,
+                     (int64_t)(sizeof(sh.u) - sizeof(sh.u.hist)) / 4);
       const int32_t nr = uni(st.nr);
       net_count(A, [&](auto &&f) { pair_items(p, nr, f); });
       __syncthreads();

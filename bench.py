@@ -20,7 +20,7 @@ plain vs learned start factor on one sweep of C4 (2D RGG n = 2^22, k = 64),
 and the quality leg (most balanced cuts, FM, contracted terminals on C5).
 
 ``python bench.py --summarize KIND DIR ...`` turns rocprofv3 output copied
-back from the GPU machine into the summaries under profiles/ (see summarize()).
+back from the machine with the GPU into the summaries under profiles/ (see summarize()).
 """
 from __future__ import annotations
 
@@ -645,7 +645,7 @@ def summarize(argv):
         rows = _csv_rows(src, "kernel_stats.csv")
         rows.sort(key=lambda r: -float(_col(r, "TotalDurationNs")))
         lines = [f"# Kernel time, {work}", "",
-                 "Command (from the repository root on the GPU box):", "", "```", cmd, "```", "",
+                 "Command (from the repository root on the machine with the GPU):", "", "```", cmd, "```", "",
                  "| kernel | calls | total ms | average us | % |", "|---|---:|---:|---:|---:|"]
         for r in rows:
             lines.append(f"| {_col(r, 'Name')} | {_col(r, 'Calls')} | "
@@ -674,9 +674,9 @@ def summarize(argv):
     res = {}
     for counter, root in (("FETCH_SIZE", fdir), ("WRITE_SIZE", wdir)):
         vals, names = per_dispatch(root, counter)
-        flow = [v for d, v in vals.items() if "k_flow" in names[d]]
+        flow = [v for d, v in vals.items() if "k_flow<" in names[d]]
         copies = [v for d, v in vals.items() if "copy" in names[d].lower()]
-        kname = next(names[d] for d in vals if "k_flow" in names[d])
+        kname = next(names[d] for d in vals if "k_flow<" in names[d])
         res[counter] = (sum(flow) / len(flow), len(flow), max(copies), kname)
     probe_kib = COPY_PROBE_BYTES / 1024
     fscale = probe_kib / res["FETCH_SIZE"][2]
@@ -715,7 +715,7 @@ def summarize(argv):
         json.dump(d, f, indent=1)
     md = [f"# HBM traffic of {kname}, {work}", "",
           "Two counter passes, FETCH_SIZE then WRITE_SIZE, each its own run of this command "
-          "(from the repository root on the GPU box):", "", "```", cmd, "```", "",
+          "(from the repository root on the machine with the GPU):", "", "```", cmd, "```", "",
           "Calibration: one 512 MiB device copy in the same run (`--copy-probe`).", "",
           "| | FETCH_SIZE KiB | WRITE_SIZE KiB |", "|---|---:|---:|",
           f"| copy of 512 MiB | {res['FETCH_SIZE'][2]:.1f} | {res['WRITE_SIZE'][2]:.1f} |",

@@ -266,8 +266,9 @@ typedef struct fr_context fr_context;
  * queued on `hip_stream` (a hipStream_t; NULL = the null stream) and run on
  * the context's own stream.  Device scratch is allocated lazily and grows
  * with the largest graph seen: per-pair arenas and corridor marks take
- * (speculative factors per pair) x (n vertices, 2m arcs) slots, at most
- * 2^28 vertex and 2^29 arc slots. */
+ * (speculative factors per pair) x n vertex slots and as many times
+ * max(2m, 8n + m) arc slots of 16 bytes (a network row per vertex; 2m where
+ * that much memory isn't there), at most 2^28 vertex and 2^29 arc slots. */
 int32_t fr_create(int32_t device, void *hip_stream, fr_context **ctx);
 int32_t fr_destroy(fr_context *ctx);
 const char *fr_strerror(int32_t code);

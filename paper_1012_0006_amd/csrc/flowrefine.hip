@@ -129,9 +129,16 @@ static void dfree(void *p) {
   if (p) (void)hipFree(p);
 }
 
+// On failure *p is null, and the runtime's sticky error is taken back: it
+// would be reported by the next hipGetLastError, that of a later call.
 template <typename T>
 static hipError_t dalloc(T **p, int64_t count) {
-  return hipMalloc((void **)p, sizeof(T) * (size_t)(count > 0 ? count : 1));
+  const hipError_t e = hipMalloc((void **)p, sizeof(T) * (size_t)(count > 0 ? count : 1));
+  if (e != hipSuccess) {
+    *p = nullptr;
+    (void)hipGetLastError();
+  }
+  return e;
 }
 
 static void free_vertex_arc(DevBufs &d) {
@@ -199,7 +206,6 @@ static int32_t ensure_capacity(fr_context *c, int64_t n, int64_t narcs, int64_t 
     A_(ga, ac); A_(gw, ac);
     A_(arc, sac);
     if (e == hipErrorOutOfMemory && sac > slots * narcs) {  // the arcs alone: networks in CSR form
-      (void)hipGetLastError();
       sac = std::max(slots * narcs, (int64_t)1);
       d.arc_small = true;
       e = dalloc(&d.arc, sac);
@@ -1907,7 +1913,7 @@ extern "C" int32_t fr_autotune(fr_context *c, const fr_graph *g, const int32_t *
   const fr_tuning keep = c->tune;
   int32_t *dpart = nullptr;
   HIPCHK(hipSetDevice(c->device));
-  HIPCHK(hipMalloc((void **)&dpart, sizeof(int32_t) * (size_t)g->n));
+  if (dalloc(&dpart, g->n) != hipSuccess) return FR_E_OOM;
   std::vector<fr_result> res((size_t)npairs), ref((size_t)npairs);
   double best_ms = 1e300;
   int32_t best = -1;

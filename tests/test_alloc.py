@@ -1,0 +1,106 @@
+"""The library's device allocations on the CPU, over a stand-in for the HIP
+runtime (fake_hip.cpp): calls on a card of any memory size either report
+FR_E_OOM or launch rounds whose buffers all exist and are large enough, and a
+call that failed leaves nothing behind that a later call would use."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+import paper_1012_0006_amd as fr
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+# Runs in a process of its own, where nothing has loaded the real runtime.
+CHILD = r"""
+import ctypes, sys, types
+import numpy as np
+root, so, scenario = sys.argv[1:4]
+hip = ctypes.CDLL(so, mode=ctypes.RTLD_GLOBAL)
+for f in ("used", "arenas", "bad", "arc_cap"):
+    getattr(hip, "fake_" + f).restype = ctypes.c_int64
+hip.fake_budget.argtypes = [ctypes.c_int64]
+sys.modules["torch"] = types.ModuleType("torch")
+sys.path.insert(0, root)
+import paper_1012_0006_amd as fr
+
+OOM = -7
+MB = 1 << 20
+LARGE = 1 << 40
+
+
+class G:
+    # a graph of n vertices and about deg arcs each: the kernels do not run,
+    # only the sizes matter
+    def __init__(self, n, deg):
+        self.n = n
+        self.xadj = (np.arange(n + 1, dtype=np.int64) * deg).astype(np.int32)
+        arcs = int(self.xadj[-1])
+        self.adjncy = np.zeros(arcs, np.int32)
+        self.adjwgt = np.ones(arcs, np.int32)
+        self.vwgt = np.ones(n, np.int32)
+
+
+def prm(**kw):
+    return fr.params(**dict(dict(alpha=16, alpha_max=16, adaptive=1, max_iters=4), **kw))
+
+
+def call(ctx, g, k=4, pairs=((0, 1), (2, 3)), sweep=False, **kw):
+    # 0, or the error code of a round of two pairs
+    part = np.zeros(g.n, np.int32)
+    try:
+        if sweep:
+            fr.flow_refine_sweep(ctx, g, part, k, prm(**kw), 1)
+        else:
+            fr.flow_refine_batch(ctx, g, part, k, pairs, prm(**kw))
+    except fr.FlowRefineError as e:
+        return e.code
+    return 0
+
+
+def context():
+    hip.fake_budget(LARGE)
+    return fr.Context(0, stream=0)
+"""
+
+SCENARIOS = {}
+
+
+def scenario(name):
+    def add(code):
+        SCENARIOS[name] = code
+        return code
+    return add
+
+
+# A failed allocation's error is the call's own: the runtime keeps it for the
+# next one that asks, and that must not be a later call.
+scenario("call_after_failure")(r"""
+ctx = context()
+hip.fake_budget(hip.fake_used() + MB)
+assert call(ctx, G(40000, 8)) == OOM
+hip.fake_budget(LARGE)
+assert call(ctx, G(40000, 8)) == 0
+assert hip.fake_bad() == 0
+""")
+
+
+@pytest.fixture(scope="module")
+def fake_hip(tmp_path_factory):
+    if not os.path.exists(fr.LIB_PATH):
+        pytest.skip("library not built")
+    so = str(tmp_path_factory.mktemp("fake") / "libfakehip.so")
+    subprocess.check_call(["g++", "-O1", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__",
+                           "-I/opt/rocm/include", "-I" + os.path.join(ROOT, "include"),
+                           "-I" + os.path.join(ROOT, "paper_1012_0006_amd", "csrc"),
+                           os.path.join(HERE, "fake_hip.cpp"), "-o", so])
+    return so
+
+
+@pytest.mark.parametrize("name", list(SCENARIOS))
+def test_allocations(fake_hip, name):
+    r = subprocess.run([sys.executable, "-c", CHILD + SCENARIOS[name], ROOT, fake_hip, name],
+                       capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-4000:]

@@ -204,8 +204,11 @@ static int32_t ensure_capacity(fr_context *c, int64_t n, int64_t narcs, int64_t 
     A_(lflag, snc);
     A_(partw, nc); A_(parts, nc); A_(gx, nc + 1); A_(gv, nc); A_(side, nc);
     A_(ga, ac); A_(gw, ac);
+    const bool others = e == hipSuccess;
     A_(arc, sac);
-    if (e == hipErrorOutOfMemory && sac > slots * narcs) {  // the arcs alone: networks in CSR form
+    // no memory for the rows (and for nothing else): the arcs alone, networks
+    // in CSR form
+    if (others && e == hipErrorOutOfMemory && sac > slots * narcs) {
       sac = std::max(slots * narcs, (int64_t)1);
       d.arc_small = true;
       e = dalloc(&d.arc, sac);

@@ -87,6 +87,32 @@ assert hip.fake_bad() == 0
 """)
 
 
+# A card that runs full in the middle of a growing call: the second graph has
+# more vertices than the first and few arcs, so the arrays that come before
+# the arc records are the larger ones.
+scenario("growth_that_fails")(r"""
+codes = set()
+dense, sparse = G(3000, 60), G(40000, 0.1)
+ctx = context()
+base = hip.fake_used()
+assert call(ctx, dense) == 0 and call(ctx, sparse) == 0
+most = hip.fake_used() - base
+ctx.close()
+for step in range(1, 97):
+    ctx = context()
+    assert call(ctx, dense) == 0
+    hip.fake_budget(base + most * step // 96)
+    a0 = hip.fake_arenas()
+    rc = call(ctx, sparse)
+    codes.add(rc)
+    assert hip.fake_bad() == 0, (step, rc)
+    assert rc in (0, OOM), (step, rc)
+    assert (hip.fake_arenas() > a0) == (rc == 0), (step, rc)
+    ctx.close()
+assert codes == {0, OOM}, codes
+""")
+
+
 @pytest.fixture(scope="module")
 def fake_hip(tmp_path_factory):
     if not os.path.exists(fr.LIB_PATH):

@@ -232,7 +232,7 @@ static int32_t ensure_capacity(fr_context *c, int64_t n, int64_t narcs, int64_t 
     d.qadj = nullptr;
     d.mtw = nullptr;
     d.mtchg = nullptr;
-    d.mtkcap = 0;
+    d.kcap = d.mtkcap = 0;
     if (dalloc(&d.blk2pair, 3 * k) != hipSuccess || dalloc(&d.bstat, 3 * k) != hipSuccess ||
         dalloc(&d.qadj, k * k) != hipSuccess)
       return FR_E_OOM;
@@ -241,16 +241,24 @@ static int32_t ensure_capacity(fr_context *c, int64_t n, int64_t narcs, int64_t 
   return FR_OK;
 }
 
+// (the old arrays stay when the new ones can't be had: every context has room
+// for one round's pairs)
 static int32_t ensure_pairs(fr_context *c, int64_t npairs) {
   DevBufs &d = c->d;
   if (npairs <= d.pcap) return FR_OK;
   const int64_t pc = std::max<int64_t>(npairs, 2 * d.pcap);
-  dfree(d.ps); dfree(d.pairs); dfree(d.alpha0); dfree(d.order);
-  d.ps = nullptr;
-  d.pairs = d.alpha0 = d.order = nullptr;
-  if (dalloc(&d.ps, pc) != hipSuccess || dalloc(&d.pairs, 2 * pc) != hipSuccess ||
-      dalloc(&d.alpha0, pc) != hipSuccess || dalloc(&d.order, pc) != hipSuccess)
+  PairState *ps = nullptr;
+  int32_t *pairs = nullptr, *alpha0 = nullptr, *order = nullptr;
+  if (dalloc(&ps, pc) != hipSuccess || dalloc(&pairs, 2 * pc) != hipSuccess ||
+      dalloc(&alpha0, pc) != hipSuccess || dalloc(&order, pc) != hipSuccess) {
+    dfree(ps); dfree(pairs); dfree(alpha0); dfree(order);
     return FR_E_OOM;
+  }
+  dfree(d.ps); dfree(d.pairs); dfree(d.alpha0); dfree(d.order);
+  d.ps = ps;
+  d.pairs = pairs;
+  d.alpha0 = alpha0;
+  d.order = order;
   d.pcap = pc;
   return FR_OK;
 }

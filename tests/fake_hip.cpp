@@ -1,8 +1,8 @@
 // Host stand-in for the HIP runtime functions that libflowrefine calls, for
 // CPU tests of its host code: device memory is zero-filled host memory within
-// a settable budget, copies are memcpy, kernels are not run.  Every launch of
-// k_arena, whose argument is a round's complete KArgs, is checked against the
-// live allocations.  Loaded with RTLD_GLOBAL ahead of the library.
+// a settable budget, copies are memcpy, kernels are not run (k_quotient: every
+// two blocks are adjacent).  Every launch of k_arena, whose argument is a
+// round's complete KArgs, is checked against the live allocations.  Loaded with RTLD_GLOBAL ahead of the library.
 #include <hip/hip_runtime_api.h>
 #include <stdio.h>
 #include <string.h>
@@ -235,10 +235,16 @@ API hipError_t __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *s, hipStream_
 }
 API hipError_t hipLaunchKernel(const void *fn, dim3, dim3, void **args, size_t, hipStream_t) {
   auto it = kernels.find(fn);
-  if (it != kernels.end() && it->second.find("k_arena") != std::string::npos) {
+  if (it == kernels.end()) return hipSuccess;
+  if (it->second.find("k_arena") != std::string::npos) {
     last = *(const KArgs *)args[0];
     arenas++;
     check_round(last);
+  } else if (it->second.find("k_quotient") != std::string::npos) {
+    const int64_t k = ((const KArgs *)args[0])->k;
+    uint8_t *q = *(uint8_t **)args[1];
+    need("qadj", q, k * k);
+    if (room(q) >= (size_t)(k * k)) memset(q, 1, (size_t)(k * k));
   }
   return hipSuccess;
 }

@@ -113,6 +113,24 @@ assert codes == {0, OOM}, codes
 """)
 
 
+# The arrays per block and per pair: what a failed growth gave back is not
+# there for the next call that would have fitted it.
+scenario("blocks_and_pairs_that_fail")(r"""
+g = G(20000, 4)
+ctx = context()
+assert call(ctx, g) == 0 and call(ctx, g, sweep=True, k=8) == 0
+for kw in (dict(k=4000), dict(k=3000), dict(k=128, sweep=True)):
+    for mb in range(5):
+        hip.fake_budget(hip.fake_used() + mb * MB)
+        assert call(ctx, g, **kw) in (0, OOM), (kw, mb)
+        hip.fake_budget(LARGE)
+        for sweep in (False, True):
+            a0 = hip.fake_arenas()
+            assert call(ctx, g, k=8, sweep=sweep) == 0 and hip.fake_arenas() > a0, (kw, mb, sweep)
+            assert hip.fake_bad() == 0, (kw, mb, sweep)
+""")
+
+
 @pytest.fixture(scope="module")
 def fake_hip(tmp_path_factory):
     if not os.path.exists(fr.LIB_PATH):

@@ -43,7 +43,7 @@ struct DevBufs {
           *SNK = nullptr, *partw = nullptr, *parts = nullptr, *gx = nullptr, *gv = nullptr;
   uint8_t *lflag = nullptr;
   int8_t *side = nullptr;
-  int32_t *mbq = nullptr;  // most balanced cut: quotient arcs, one per arc slot (lazy)
+  int32_t *mbq = nullptr;  // most balanced cut: one-way and quotient arcs (lazy)
   int64_t mbqcap = 0;
   // input checks: hub table offsets [n], table keys and weights
   int64_t *vhdir = nullptr;
@@ -76,8 +76,8 @@ struct DevBufs {
   // per round (at most FR_MAX_PAIRS pairs)
   fr_solve *trace = nullptr, *srec = nullptr;
   int32_t *ucnt = nullptr, *qctr = nullptr, *pcnt = nullptr, *act = nullptr, *nact = nullptr;
-  int64_t *voff = nullptr, *aoff = nullptr, *fstat = nullptr, *pacc = nullptr, *vpre = nullptr,
-          *cpre = nullptr, *mpre = nullptr;
+  int64_t *voff = nullptr, *aoff = nullptr, *moff = nullptr, *fstat = nullptr, *pacc = nullptr,
+          *vpre = nullptr, *cpre = nullptr, *mpre = nullptr;
   float *feats = nullptr, *probs = nullptr;
   int64_t *base = nullptr, *scal = nullptr;
   Ctl *ctl = nullptr;
@@ -379,7 +379,8 @@ extern "C" int32_t fr_create(int32_t device, void *hip_stream, fr_context **out)
   A_(act, FR_MAX_PAIRS); A_(nact, 2); A_(vpre, FR_MAX_PAIRS + 1); A_(cpre, FR_MAX_PAIRS + 1);
   A_(mpre, FR_MAX_PAIRS + 1);
   A_(srec, FR_MAX_PAIRS);
-  A_(voff, FR_MAX_PAIRS + 1); A_(aoff, FR_MAX_PAIRS + 1); A_(fstat, 4 * FR_MAX_PAIRS);
+  A_(voff, FR_MAX_PAIRS + 1); A_(aoff, FR_MAX_PAIRS + 1);
+  A_(moff, FR_MAX_PAIRS + 1); A_(fstat, 4 * FR_MAX_PAIRS);
   A_(feats, MLP_IN * FR_MAX_PAIRS); A_(probs, MLP_OUT * FR_MAX_PAIRS);
   A_(base, FR_MAX_ALPHA + 1); A_(scal, 8); A_(ctl, 1);
   A_(mlp, MLP_NPARAMS); A_(mlp_m, MLP_NPARAMS); A_(mlp_v, MLP_NPARAMS); A_(mlp_g, MLP_NPARAMS);
@@ -411,7 +412,7 @@ extern "C" int32_t fr_destroy(fr_context *c) {
                   d.trace,    d.ucnt,  d.voff, d.aoff,  d.fstat, d.feats,  d.probs,
                   d.base,     d.scal,  d.ctl,  d.mlp,   d.mlp_m, d.mlp_v,  d.mlp_g,
                   d.qctr,     d.pcnt,  d.pacc, d.act,   d.nact,  d.vpre,   d.cpre, d.mpre,
-                  d.srec,     d.mlpbuf};
+                  d.srec,     d.mlpbuf, d.moff};
   for (void *q : ptrs) dfree(q);
   if (c->h_ctl) (void)hipHostFree(c->h_ctl);
   for (int i = 0; i < 4; i++)
@@ -616,6 +617,7 @@ static KArgs call_args(fr_context *c, const DevBufs &d, const fr_graph *g, int32
   A.vmap = d.vmap;
   A.voff = d.voff;
   A.aoff = d.aoff;
+  A.moff = d.moff;
   A.ucnt = d.ucnt;
   A.uvert = d.uvert;
   A.lg = d.lg;

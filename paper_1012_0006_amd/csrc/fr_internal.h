@@ -148,9 +148,11 @@ struct KArgs {
   int32_t restart_alpha;
   int32_t stamp0;           // corridor mark of the first solve (even)
   // most balanced minimum cut: sweeps (0 = smallest source set), key seed,
-  // component graph in LDS when it fits, quotient arcs (one slot per arc slot)
+  // component graph in LDS when it fits, quotient arcs (a word per arc of the
+  // entry's blocks: words [moff[p], moff[p+1]))
   int32_t mb_reps, mb_seed, mb_lds;
   int32_t *mbq;
+  int64_t *moff;            // [P + 1]
   int32_t *mbc;             // large component graphs: 4 words per arena vertex slot
   int64_t *mpre;            // [P + 1] prefix sums of the entries' free-vertex counts
   // 2-way FM before the flow: non-improving moves before it stops (0 = off),

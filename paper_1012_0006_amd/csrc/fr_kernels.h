@@ -378,7 +378,9 @@ __global__ void __launch_bounds__(256) k_block_stats(KArgs A) {
 
 // Arena slices (prefix sums of the pairs' vertex and arc counts), the
 // largest-first order in which workgroups take the pairs, and the initial
-// pair states.  One block.
+// pair states.  One block.  The slices of the network (aoff) follow its form;
+// those of the most balanced cut's arc lists (moff) hold a word per arc in
+// either form.
 __global__ void __launch_bounds__(1024) k_arena(KArgs A) {
   __shared__ int64_t s_scan[17];
   const int64_t *bw = A.bstat, *bc = A.bstat + A.k, *ba = A.bstat + 2 * A.k;
@@ -408,15 +410,24 @@ __global__ void __launch_bounds__(1024) k_arena(KArgs A) {
     ra = block_exscan64(sa, &ta, s_scan);
     if (ta <= A.arc_cap || how == 2) break;
   }
+  auto arcs = [&](int i) { return ba[A.pairs[2 * i]] + ba[A.pairs[2 * i + 1]]; };
+  int64_t sm = 0, tm = 0, rm = 0;
+  if (A.mb_reps > 0) {
+    for (int i = lo; i < hi; i++) sm += arcs(i);
+    rm = block_exscan64(sm, &tm, s_scan);
+  }
   for (int i = lo; i < hi; i++) {
     A.voff[i] = rv;
     A.aoff[i] = ra;
+    if (A.mb_reps > 0) A.moff[i] = rm;
     rv += bc[A.pairs[2 * i]] + bc[A.pairs[2 * i + 1]];
     ra += slice(i, how);
+    rm += arcs(i);
   }
   if (threadIdx.x == 0) {
     A.voff[P] = tv;
     A.aoff[P] = ta;
+    if (A.mb_reps > 0) A.moff[P] = tm;
   }
   for (int i = threadIdx.x; i < P; i += blockDim.x) {
     const int32_t a = A.pairs[2 * i], b = A.pairs[2 * i + 1];

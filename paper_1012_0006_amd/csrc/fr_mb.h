@@ -330,7 +330,7 @@ __global__ void __launch_bounds__(256) k_mb_union(KArgs A, int32_t it) {
     int32_t *par = A.LA + vb;
     const int32_t *lo = A.lo + vb + p;
     const Arc *arc = A.arc + ab;
-    int32_t *w1 = A.mbq + ab;
+    int32_t *w1 = A.mbq + A.moff[p];
     const int32_t u = A.LB[vb + (i - A.mpre[p])];
     if (A.ps[p].rows) {
       const u64 *L = rows_of(A, p);
@@ -465,7 +465,7 @@ __global__ void __launch_bounds__(MB_TPB) k_mb(KArgs A, int32_t it) {
   }
   int32_t *par = V.LA;        // [nr]: -1 outside M; class parent, later the component
   const int32_t *ml = V.LB;   // the free vertices M
-  int32_t *w1 = A.mbq + A.aoff[p];  // one-way arcs inside M, then (device path) quotient arcs
+  int32_t *w1 = A.mbq + A.moff[p];  // one-way arcs inside M, then (device path) quotient arcs
 
   // ---- 1. (k_mb_union did the union-find and listed the one-way arcs)
   // compression (every free vertex points at its class root, the class's
@@ -519,7 +519,7 @@ __global__ void __launch_bounds__(MB_TPB) k_mb(KArgs A, int32_t it) {
     __syncthreads();
     qoff = V.ex;
   }
-  int32_t *qarc = lt ? sh.u2.q.qarc : w1 + n1w;  // eq <= n1w <= arc slots / 2
+  int32_t *qarc = lt ? sh.u2.q.qarc : w1 + n1w;  // eq <= n1w <= half of the slice's words
   int32_t *cur = lt ? sh.u1.t.cpos : V.SNK;
   for (int32_t q = threadIdx.x; q < nq; q += blockDim.x) cur[q] = qoff[q];
   __syncthreads();

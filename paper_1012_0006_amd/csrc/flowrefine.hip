@@ -65,7 +65,6 @@ struct DevBufs {
   // per arc
   int32_t *ga = nullptr, *gw = nullptr;
   Arc *arc = nullptr;  // corridor arcs
-  bool arc_small = false;  // no memory for a network row per vertex
   // per block
   int32_t *blk2pair = nullptr;
   int64_t *bstat = nullptr;  // [3k]
@@ -178,6 +177,36 @@ static void free_vertex_arc(DevBufs &d) {
   d.ncap = d.acap = d.sncap = d.sacap = 0;
 }
 
+// Whether that many more bytes of device memory could be had (a buffer that
+// grows is given back first: its old size doesn't count).
+static bool memory_for(int64_t bytes) {
+  size_t have = 0, total = 0;
+  if (bytes <= 0) return true;
+  if (hipMemGetInfo(&have, &total) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return (int64_t)have >= bytes;
+}
+
+// The arc records: `arcs` of them at least, and `rows` (the network rows'
+// room) where there is memory for that; networks that don't fit what is
+// there take the CSR form.  Without the memory, an array that holds the arcs
+// stays as it is.
+static int32_t ensure_arcs(DevBufs &d, int64_t arcs, int64_t rows, int64_t keep) {
+  if (d.sacap >= rows && d.arc) return FR_OK;
+  if (d.arc && d.sacap >= arcs && !memory_for((rows - d.sacap) * (int64_t)sizeof(Arc))) return FR_OK;
+  dfree(d.arc);
+  d.arc = nullptr;
+  d.sacap = 0;
+  for (const int64_t cap : {std::max(rows, keep), rows, std::max(arcs, (int64_t)1)})
+    if (dalloc(&d.arc, cap) == hipSuccess) {
+      d.sacap = cap;
+      return FR_OK;
+    }
+  return FR_E_OOM;
+}
+
 // Graph-sized buffers (staged copies, partitions, side codes) for n vertices
 // and narcs arcs; arena-sized ones (per-entry slices, corridor marks) for
 // `slots` entries per vertex and per arc.
@@ -188,13 +217,12 @@ static int32_t ensure_capacity(fr_context *c, int64_t n, int64_t narcs, int64_t 
   // at most one more per 16 arcs) where they are more, and the rounding of
   // each entry's slice to whole cache lines
   const int64_t sn = slots * n;
-  int64_t sa = slots * std::max(narcs, (int64_t)(ROW_WORDS / 2) * n + narcs / 2 + 1) +
-               8 * FR_MAX_PAIRS;
-  if (n > d.ncap || narcs > d.acap || sn > d.sncap || slots * narcs > d.sacap ||
-      (sa > d.sacap && !d.arc_small)) {
+  const int64_t rows = slots * std::max(narcs, (int64_t)(ROW_WORDS / 2) * n + narcs / 2 + 1) +
+                       8 * FR_MAX_PAIRS;
+  const int64_t keep = d.sacap;
+  if (n > d.ncap || narcs > d.acap || sn > d.sncap) {
     const int64_t nc = std::max(n, d.ncap), ac = std::max(narcs, d.acap);
     const int64_t snc = std::max(sn, d.sncap);
-    int64_t sac = std::max(sa, d.sacap);
     free_vertex_arc(d);
     hipError_t e = hipSuccess;
 #define A_(p, cnt) \
@@ -204,15 +232,6 @@ static int32_t ensure_capacity(fr_context *c, int64_t n, int64_t narcs, int64_t 
     A_(lflag, snc);
     A_(partw, nc); A_(parts, nc); A_(gx, nc + 1); A_(gv, nc); A_(side, nc);
     A_(ga, ac); A_(gw, ac);
-    const bool others = e == hipSuccess;
-    A_(arc, sac);
-    // no memory for the rows (and for nothing else): the arcs alone, networks
-    // in CSR form
-    if (others && e == hipErrorOutOfMemory && sac > slots * narcs) {
-      sac = std::max(slots * narcs, (int64_t)1);
-      d.arc_small = true;
-      e = dalloc(&d.arc, sac);
-    }
 #undef A_
     if (e != hipSuccess) {
       free_vertex_arc(d);
@@ -222,9 +241,10 @@ static int32_t ensure_capacity(fr_context *c, int64_t n, int64_t narcs, int64_t 
     d.ncap = nc;
     d.acap = ac;
     d.sncap = snc;
-    d.sacap = sac;
     c->stamp = 2;
   }
+  const int32_t rc = ensure_arcs(d, slots * narcs, rows, keep);
+  if (rc) return rc;
   if (k > d.kcap) {
     dfree(d.blk2pair); dfree(d.bstat); dfree(d.qadj); dfree(d.mtw); dfree(d.mtchg);
     d.blk2pair = nullptr;

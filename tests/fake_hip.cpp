@@ -18,7 +18,7 @@ static std::map<char *, size_t> live;  // device allocations
 static size_t used = 0, budget = (size_t)1 << 40;
 static std::map<const void *, std::string> kernels;
 static hipError_t last_error = hipSuccess;
-static int64_t arenas = 0, bad = 0;
+static int64_t arenas = 0, bad = 0, mallocs = 0;
 static KArgs last;
 
 // bytes from p to the end of its allocation (0: not in a live one)
@@ -88,11 +88,13 @@ API void fake_budget(int64_t bytes) { budget = (size_t)bytes; }
 API int64_t fake_used() { return (int64_t)used; }
 API int64_t fake_arenas() { return arenas; }
 API int64_t fake_bad() { return bad; }
+API int64_t fake_mallocs() { return mallocs; }
 API int64_t fake_arc_cap() { return last.arc_cap; }
 API int32_t fake_all_rows() { return last.all_rows; }
 API int32_t fake_slots() { return last.W; }
 
 API hipError_t hipMalloc(void **p, size_t n) {
+  mallocs++;
   n = (std::max<size_t>(n, 1) + 4095) & ~(size_t)4095;
   if (used + n > budget) {
     *p = nullptr;

@@ -19,7 +19,7 @@ import ctypes, sys, types
 import numpy as np
 root, so, scenario = sys.argv[1:4]
 hip = ctypes.CDLL(so, mode=ctypes.RTLD_GLOBAL)
-for f in ("used", "arenas", "bad", "arc_cap"):
+for f in ("used", "arenas", "bad", "mallocs", "arc_cap"):
     getattr(hip, "fake_" + f).restype = ctypes.c_int64
 hip.fake_budget.argtypes = [ctypes.c_int64]
 sys.modules["torch"] = types.ModuleType("torch")
@@ -128,6 +128,33 @@ for kw in (dict(k=4000), dict(k=3000), dict(k=128, sweep=True)):
             a0 = hip.fake_arenas()
             assert call(ctx, g, k=8, sweep=sweep) == 0 and hip.fake_arenas() > a0, (kw, mb, sweep)
             assert hip.fake_bad() == 0, (kw, mb, sweep)
+""")
+
+
+# Networks without rows last as long as the memory is short, and a call that
+# can't have them allocates nothing anew.
+scenario("rows_when_there_is_memory")(r"""
+g, thin = G(40000, 12), G(40000, 1)
+ctx = context()
+assert call(ctx, g) == 0
+rows, most = hip.fake_arc_cap(), hip.fake_used()
+assert hip.fake_all_rows() == 1
+ctx.close()
+ctx = context()
+hip.fake_budget(most - MB)
+assert call(ctx, g) == 0
+arcs = hip.fake_arc_cap()
+assert arcs == hip.fake_slots() * 40000 * 12 < rows and hip.fake_all_rows() == 0
+before = hip.fake_mallocs()
+assert call(ctx, g) == 0 and call(ctx, g) == 0
+assert hip.fake_mallocs() == before and hip.fake_arc_cap() == arcs
+hip.fake_budget(LARGE)
+assert call(ctx, g) == 0
+assert hip.fake_arc_cap() == rows and hip.fake_all_rows() == 1
+# a graph of fewer arcs and vertices whose rows the small array holds, and one
+# whose rows need more than it
+assert call(ctx, thin) == 0 and hip.fake_all_rows() == 1
+assert hip.fake_bad() == 0
 """)
 
 

@@ -268,7 +268,9 @@ typedef struct fr_context fr_context;
  * with the largest graph seen: per-pair arenas and corridor marks take
  * (speculative factors per pair) x n vertex slots and as many times
  * max(2m, 8n + m) arc slots of 16 bytes (a network row per vertex; 2m where
- * that much memory isn't there), at most 2^28 vertex and 2^29 arc slots. */
+ * that much memory isn't there).  The factors are fewer where they would take
+ * more than 2^28 vertex slots or 2m times them more than 2^29 arc slots; rows
+ * take at most 2^29 arc slots. */
 int32_t fr_create(int32_t device, void *hip_stream, fr_context **ctx);
 int32_t fr_destroy(fr_context *ctx);
 const char *fr_strerror(int32_t code);

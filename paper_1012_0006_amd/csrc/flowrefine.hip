@@ -32,6 +32,7 @@ static thread_local hipError_t last_hip_error = hipSuccess;
 
 #define FR_MAX_PAIRS 4096  // pairs of one round (one launch)
 #define FR_MAX_K 8192
+#define ARC_SLOTS_MAX ((int64_t)1 << 29)  // arc records of all entries (speculation), rows included
 #define FR_MAX_BLOCKS_PER_CU 8
 
 struct DevBufs {
@@ -214,11 +215,15 @@ static int32_t ensure_capacity(fr_context *c, int64_t n, int64_t narcs, int64_t 
                                int64_t slots = 1) {
   DevBufs &d = c->d;
   // arc slots: the arcs, or the network rows (fr_rows.h: one per vertex and
-  // at most one more per 16 arcs) where they are more, and the rounding of
-  // each entry's slice to whole cache lines
-  const int64_t sn = slots * n;
-  const int64_t rows = slots * std::max(narcs, (int64_t)(ROW_WORDS / 2) * n + narcs / 2 + 1) +
-                       8 * FR_MAX_PAIRS;
+  // at most one more per 16 arcs) where they are more, up to ARC_SLOTS_MAX;
+  // and the rounding of each entry's slice to whole cache lines.  A graph
+  // beyond the bound still gets rows wherever a corridor's fit its entry's
+  // slice: 8 nr records of the two blocks' arc count.
+  const int64_t sn = slots * n, arcs = slots * narcs;
+  const int64_t rows =
+      std::max(arcs, std::min(slots * ((int64_t)(ROW_WORDS / 2) * n + narcs / 2 + 1),
+                              ARC_SLOTS_MAX - 8 * FR_MAX_PAIRS)) +
+      8 * FR_MAX_PAIRS;
   const int64_t keep = d.sacap;
   if (n > d.ncap || narcs > d.acap || sn > d.sncap) {
     const int64_t nc = std::max(n, d.ncap), ac = std::max(narcs, d.acap);
@@ -243,7 +248,7 @@ static int32_t ensure_capacity(fr_context *c, int64_t n, int64_t narcs, int64_t 
     d.sncap = snc;
     c->stamp = 2;
   }
-  const int32_t rc = ensure_arcs(d, slots * narcs, rows, keep);
+  const int32_t rc = ensure_arcs(d, arcs, rows, keep);
   if (rc) return rc;
   if (k > d.kcap) {
     dfree(d.blk2pair); dfree(d.bstat); dfree(d.qadj); dfree(d.mtw); dfree(d.mtchg);
@@ -1195,7 +1200,7 @@ static int32_t speculation_slots(const fr_context *c, const fr_params *p, int32_
   for (int32_t a = p->alpha_max; a >= 1; a >>= 1) W++;
   const int64_t slots = (int64_t)c->num_cus * c->tune.blocks_per_cu;
   while (W > 1 && ((int64_t)npairs * W > slots || (int64_t)npairs * W > FR_MAX_PAIRS ||
-                   W * n > (1ll << 28) || W * narcs > (1ll << 29)))
+                   W * n > (1ll << 28) || W * narcs > ARC_SLOTS_MAX))
     W--;
   return W;
 }

@@ -158,6 +158,18 @@ assert hip.fake_bad() == 0
 """)
 
 
+# The documented bound of the arc records: 2^29 while the arcs themselves take
+# no more.
+scenario("bound_of_the_arc_slots")(r"""
+g = G(14000000, 1)
+ctx = context()
+assert call(ctx, g, sweep=True, k=2, pairs=()) == 0
+assert hip.fake_slots() == 5 and hip.fake_bad() == 0
+assert 5 * 14000000 <= hip.fake_arc_cap() <= 1 << 29
+assert hip.fake_all_rows() == 0
+""")
+
+
 @pytest.fixture(scope="module")
 def fake_hip(tmp_path_factory):
     if not os.path.exists(fr.LIB_PATH):

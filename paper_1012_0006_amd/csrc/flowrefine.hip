@@ -66,6 +66,7 @@ struct DevBufs {
   // per arc
   int32_t *ga = nullptr, *gw = nullptr;
   Arc *arc = nullptr;  // corridor arcs
+  int64_t arcs = 0;    // records that the last call's arcs alone take
   // per block
   int32_t *blk2pair = nullptr;
   int64_t *bstat = nullptr;  // [3k]
@@ -208,6 +209,26 @@ static int32_t ensure_arcs(DevBufs &d, int64_t arcs, int64_t rows, int64_t keep)
   return FR_E_OOM;
 }
 
+// dalloc for a call's other buffers, which come after the arc records: short
+// of memory, the rows are given back (networks in CSR form) before it fails.
+// KArgs made before it have to take d.arc and d.sacap again (take_arcs).
+template <typename T>
+static hipError_t dalloc_late(DevBufs &d, T **p, int64_t count) {
+  hipError_t e = dalloc(p, count);
+  const int64_t arcs = std::max(d.arcs, (int64_t)1);
+  if (e != hipErrorOutOfMemory || !d.arc || d.sacap <= arcs) return e;
+  dfree(d.arc);
+  d.sacap = 0;
+  if ((e = dalloc(&d.arc, arcs)) != hipSuccess) return e;
+  d.sacap = arcs;
+  return dalloc(p, count);
+}
+
+static void take_arcs(KArgs &A, const DevBufs &d) {
+  A.arc = d.arc;
+  A.arc_cap = d.sacap;
+}
+
 // Graph-sized buffers (staged copies, partitions, side codes) for n vertices
 // and narcs arcs; arena-sized ones (per-entry slices, corridor marks) for
 // `slots` entries per vertex and per arc.
@@ -248,6 +269,7 @@ static int32_t ensure_capacity(fr_context *c, int64_t n, int64_t narcs, int64_t 
     d.sncap = snc;
     c->stamp = 2;
   }
+  d.arcs = arcs;
   const int32_t rc = ensure_arcs(d, arcs, rows, keep);
   if (rc) return rc;
   if (k > d.kcap) {
@@ -258,8 +280,8 @@ static int32_t ensure_capacity(fr_context *c, int64_t n, int64_t narcs, int64_t 
     d.mtw = nullptr;
     d.mtchg = nullptr;
     d.kcap = d.mtkcap = 0;
-    if (dalloc(&d.blk2pair, 3 * k) != hipSuccess || dalloc(&d.bstat, 3 * k) != hipSuccess ||
-        dalloc(&d.qadj, k * k) != hipSuccess)
+    if (dalloc_late(d, &d.blk2pair, 3 * k) != hipSuccess || dalloc_late(d, &d.bstat, 3 * k) != hipSuccess ||
+        dalloc_late(d, &d.qadj, k * k) != hipSuccess)
       return FR_E_OOM;
     d.kcap = k;
   }
@@ -274,8 +296,8 @@ static int32_t ensure_pairs(fr_context *c, int64_t npairs) {
   const int64_t pc = std::max<int64_t>(npairs, 2 * d.pcap);
   PairState *ps = nullptr;
   int32_t *pairs = nullptr, *alpha0 = nullptr, *order = nullptr;
-  if (dalloc(&ps, pc) != hipSuccess || dalloc(&pairs, 2 * pc) != hipSuccess ||
-      dalloc(&alpha0, pc) != hipSuccess || dalloc(&order, pc) != hipSuccess) {
+  if (dalloc_late(d, &ps, pc) != hipSuccess || dalloc_late(d, &pairs, 2 * pc) != hipSuccess ||
+      dalloc_late(d, &alpha0, pc) != hipSuccess || dalloc_late(d, &order, pc) != hipSuccess) {
     dfree(ps); dfree(pairs); dfree(alpha0); dfree(order);
     return FR_E_OOM;
   }
@@ -654,8 +676,7 @@ static KArgs call_args(fr_context *c, const DevBufs &d, const fr_graph *g, int32
   A.LB = d.LB;
   A.SNK = d.SNK;
   A.lflag = d.lflag;
-  A.arc = d.arc;
-  A.arc_cap = d.sacap;
+  take_arcs(A, d);
   A.ctl = d.ctl;
   A.tpv = c->tune.tpv;
   A.relabel_period = c->tune.relabel_period;
@@ -699,7 +720,7 @@ static int32_t validate_graph(fr_context *c, const KArgs &A, int64_t narcs, bool
         dfree(d.vhdir);
         d.vhdir = nullptr;
         d.vhcap = 0;
-        if (dalloc(&d.vhdir, A.n) != hipSuccess) return FR_E_OOM;
+        if (dalloc_late(d, &d.vhdir, A.n) != hipSuccess) return FR_E_OOM;
         d.vhcap = A.n;
       }
       if (d.vtcap < slots) {
@@ -707,7 +728,7 @@ static int32_t validate_graph(fr_context *c, const KArgs &A, int64_t narcs, bool
         dfree(d.vw);
         d.vkey = d.vw = nullptr;
         d.vtcap = 0;
-        if (dalloc(&d.vkey, slots) != hipSuccess || dalloc(&d.vw, slots) != hipSuccess)
+        if (dalloc_late(d, &d.vkey, slots) != hipSuccess || dalloc_late(d, &d.vw, slots) != hipSuccess)
           return FR_E_OOM;
         d.vtcap = slots;
       }
@@ -737,6 +758,7 @@ static int32_t call_constants(fr_context *c, KArgs &A, int64_t narcs, const fr_p
   if (c->validate) {
     int32_t rc = validate_graph(c, A, narcs, may_alloc);
     if (rc) return rc;
+    if (may_alloc) take_arcs(A, d);
   }
   hipLaunchKernelGGL(k_graph_stats, dim3(sblocks), dim3(256), 0, st, A, narcs);
   HIPCHK(hipGetLastError());
@@ -1089,8 +1111,8 @@ static int32_t stage(fr_context *c, const fr_graph *g, int32_t *part, int32_t k,
   return FR_OK;
 }
 
-// Quotient-arc slots of the most balanced cut (one per arena arc slot) and
-// the component graphs too large for LDS (four words per arena vertex slot),
+// Arc lists of the most balanced cut (a word per arc of every entry) and the
+// component graphs too large for LDS (four words per arena vertex slot),
 // allocated on first use.
 static int32_t ensure_mb(fr_context *c, const fr_params *p) {
   DevBufs &d = c->d;
@@ -1099,7 +1121,7 @@ static int32_t ensure_mb(fr_context *c, const fr_params *p) {
     dfree(d.fmq);
     d.fmg = d.fmq = nullptr;
     d.fmcap = 0;
-    if (dalloc(&d.fmg, d.ncap) != hipSuccess || dalloc(&d.fmq, d.ncap) != hipSuccess)
+    if (dalloc_late(d, &d.fmg, d.ncap) != hipSuccess || dalloc_late(d, &d.fmq, d.ncap) != hipSuccess)
       return FR_E_OOM;
     d.fmcap = d.ncap;
   }
@@ -1112,10 +1134,10 @@ static int32_t ensure_mb(fr_context *c, const fr_params *p) {
       dfree(d.mtr);
       d.mtr = nullptr;
       d.mtncap = 0;
-      if (dalloc(&d.mtt, d.ncap) != hipSuccess || dalloc(&d.mtb, d.ncap) != hipSuccess ||
-          dalloc(&d.mtq, d.ncap) != hipSuccess || dalloc(&d.mth, d.ncap) != hipSuccess ||
-          dalloc(&d.mtv, d.ncap) != hipSuccess || dalloc(&d.mtf, d.ncap) != hipSuccess ||
-          dalloc(&d.mtr, d.ncap) != hipSuccess)
+      if (dalloc_late(d, &d.mtt, d.ncap) != hipSuccess || dalloc_late(d, &d.mtb, d.ncap) != hipSuccess ||
+          dalloc_late(d, &d.mtq, d.ncap) != hipSuccess || dalloc_late(d, &d.mth, d.ncap) != hipSuccess ||
+          dalloc_late(d, &d.mtv, d.ncap) != hipSuccess || dalloc_late(d, &d.mtf, d.ncap) != hipSuccess ||
+          dalloc_late(d, &d.mtr, d.ncap) != hipSuccess)
         return FR_E_OOM;
       // touched stamps start below every stamp in use, queue slots at -1
       HIPCHK(hipMemset(d.mtt, 0, sizeof(int32_t) * (size_t)d.ncap));
@@ -1128,7 +1150,7 @@ static int32_t ensure_mb(fr_context *c, const fr_params *p) {
       dfree(d.mtk2);
       d.mtk = d.mtk2 = nullptr;
       d.mtscap = 0;
-      if (dalloc(&d.mtk, d.sncap) != hipSuccess || dalloc(&d.mtk2, d.sncap) != hipSuccess)
+      if (dalloc_late(d, &d.mtk, d.sncap) != hipSuccess || dalloc_late(d, &d.mtk2, d.sncap) != hipSuccess)
         return FR_E_OOM;
       d.mtscap = d.sncap;
     }
@@ -1137,24 +1159,24 @@ static int32_t ensure_mb(fr_context *c, const fr_params *p) {
       dfree(d.mtchg);
       d.mtw = nullptr;
       d.mtchg = nullptr;
-      if (dalloc(&d.mtw, d.kcap) != hipSuccess || dalloc(&d.mtchg, d.kcap) != hipSuccess)
+      if (dalloc_late(d, &d.mtw, d.kcap) != hipSuccess || dalloc_late(d, &d.mtchg, d.kcap) != hipSuccess)
         return FR_E_OOM;
       d.mtkcap = d.kcap;
     }
   }
   if (p->mb_reps <= 0) return FR_OK;
-  if (d.mbqcap < d.sacap) {
+  if (d.mbqcap < d.arcs) {
     dfree(d.mbq);
     d.mbq = nullptr;
     d.mbqcap = 0;
-    if (dalloc(&d.mbq, d.sacap) != hipSuccess) return FR_E_OOM;
-    d.mbqcap = d.sacap;
+    if (dalloc_late(d, &d.mbq, d.arcs) != hipSuccess) return FR_E_OOM;
+    d.mbqcap = d.arcs;
   }
   if (d.mbccap < d.sncap) {
     dfree(d.mbc);
     d.mbc = nullptr;
     d.mbccap = 0;
-    if (dalloc(&d.mbc, 4 * d.sncap) != hipSuccess) return FR_E_OOM;
+    if (dalloc_late(d, &d.mbc, 4 * d.sncap) != hipSuccess) return FR_E_OOM;
     d.mbccap = d.sncap;
   }
   return FR_OK;
@@ -1547,6 +1569,7 @@ extern "C" int32_t flow_refine_sweep(fr_context *c, const fr_graph *g, int32_t *
     const int64_t total = (int64_t)pairs.size() / 2;
     if (total == 0) break;
     if ((rc = ensure_pairs(c, total))) return rc;
+    take_arcs(A, d);
     std::vector<int32_t> a0((size_t)total, p->alpha);
     HIPCHK(hipMemcpyAsync(d.pairs, pairs.data(), sizeof(int32_t) * pairs.size(),
                           hipMemcpyHostToDevice, st));
@@ -1729,7 +1752,7 @@ static int32_t mlp_alloc(fr_context *c, MlpScratch &s, int64_t n, int64_t grad_n
       dfree(d.mlpbuf);
       d.mlpbuf = nullptr;
       d.mlpcap = 0;
-      if (dalloc(&d.mlpbuf, (int64_t)off) != hipSuccess) return FR_E_OOM;
+      if (dalloc_late(d, &d.mlpbuf, (int64_t)off) != hipSuccess) return FR_E_OOM;
       d.mlpcap = off;
     }
   }
@@ -1951,7 +1974,7 @@ extern "C" int32_t fr_autotune(fr_context *c, const fr_graph *g, const int32_t *
   const fr_tuning keep = c->tune;
   int32_t *dpart = nullptr;
   HIPCHK(hipSetDevice(c->device));
-  if (dalloc(&dpart, g->n) != hipSuccess) return FR_E_OOM;
+  if (dalloc_late(c->d, &dpart, g->n) != hipSuccess) return FR_E_OOM;
   std::vector<fr_result> res((size_t)npairs), ref((size_t)npairs);
   double best_ms = 1e300;
   int32_t best = -1;

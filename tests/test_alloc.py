@@ -170,6 +170,65 @@ assert hip.fake_all_rows() == 0
 """)
 
 
+# Rows never take the memory that a call's other buffers need: with an option,
+# a call fits wherever it fits without it and the option's own buffers do.
+# (Buffers of the call: arc lists, component graphs; gains, queue positions;
+# the multi-try arrays; neighbour tables of the input checks' hubs are not
+# allocated here.)
+scenario("options_beside_the_rows")(r"""
+def least(g, kw, sweep):
+    lo, hi = 0, 256  # in units of 256 KB
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        ctx = context()
+        hip.fake_budget(hip.fake_used() + mid * MB // 4)
+        rc = call(ctx, g, sweep=sweep, **kw)
+        assert rc in (0, OOM) and hip.fake_bad() == 0, (kw, mid, rc)
+        ctx.close()
+        lo, hi = (lo, mid) if rc == 0 else (mid, hi)
+    return hi * MB // 4
+
+
+n, deg, W = 40000, 6, 5
+g = G(n, deg)
+own = [(dict(mb_reps=4), 4 * W * n * deg + 16 * W * n), (dict(fm_limit=20), 8 * n),
+       (dict(mt_alpha=5), 32 * n + 16 * W * n)]
+for sweep in (False, True):
+    plain = least(g, {}, sweep)
+    for kw, bytes in own:
+        assert least(g, kw, sweep) <= plain + bytes + MB // 2, (kw, sweep)
+""")
+
+
+# All of it together: a card that runs full at any of the allocations of a
+# series of calls.
+scenario("any_memory_size")(r"""
+codes = set()
+small, dense, sparse = G(1000, 4), G(3000, 60), G(40000, 0.5)
+for options in (dict(), dict(mb_reps=4), dict(fm_limit=20), dict(mt_alpha=5)):
+    ctx = context()
+    base = hip.fake_used()
+    call(ctx, dense, **options), call(ctx, sparse, **options)
+    most = hip.fake_used() - base
+    ctx.close()
+    for step in range(1, 49):
+        ctx = context()
+        hip.fake_budget(hip.fake_used() + most * step // 48)
+        for g in (small, dense, sparse, dense):
+            a0 = hip.fake_arenas()
+            rc = call(ctx, g, **options)
+            codes.add(rc)
+            assert rc in (0, OOM), (options, step, g.n, rc)
+            assert (hip.fake_arenas() > a0) == (rc == 0), (options, step, g.n, rc)
+            assert hip.fake_bad() == 0, (options, step, g.n)
+        hip.fake_budget(LARGE)
+        assert call(ctx, sparse, **options) == 0, (options, step)
+        assert hip.fake_bad() == 0, (options, step)
+        ctx.close()
+assert codes == {0, OOM}, codes
+""")
+
+
 @pytest.fixture(scope="module")
 def fake_hip(tmp_path_factory):
     if not os.path.exists(fr.LIB_PATH):

@@ -119,7 +119,9 @@ struct CsrSolver {
     }
   }
 
-  __device__ __forceinline__ void count_work_done() {}
+  // (its steps count as they go)
+  __device__ __forceinline__ void count_step() {}
+  __device__ __forceinline__ void count_end() {}
 };
 
 // ---- row form ------------------------------------------------------------
@@ -143,9 +145,7 @@ struct RowSolver {
   int32_t *ls;  // LDS heads of the two lists
   const int32_t wave;
   int32_t from = 1, c_next = 1;  // list read, counter of the list written
-  // vertices and arcs touched by this thread's lanes: passes, relabels, closure
-  int32_t wi = 0, wa[3] = {0, 0, 0};
-  int32_t gr_items = 0, cl_items = 0;
+  RowWork work;
   uint32_t ahead = 0;
 
   __device__ __forceinline__ RowSolver(const KArgs &A_, const PairView &V_, SolveShared<TPB> &sh_,
@@ -332,9 +332,9 @@ struct RowSolver {
       lev = 0;
     }
     while (cnt > 0) {
-      gr_items += cnt;
+      work.gr_items += cnt;
       by_row_width<TPB>(cnt, [&](auto W) {
-        level<decltype(W)::g, true, true>(cnt, lev + 1, wa[1]);
+        level<decltype(W)::g, true, true>(cnt, lev + 1, work.arcs[1]);
       });
       cnt = advance();
       lev++;
@@ -411,8 +411,8 @@ struct RowSolver {
       e = group_first<G>(e);
       const bool work = valid && d < NL && e > 0;
       if (!work) deg = 0;
-      wi += deg > 0 ? 1 : 0;
-      wa[0] += deg;
+      this->work.items += deg > 0 ? 1 : 0;
+      this->work.arcs[0] += deg;
       int32_t erem = work ? e : 0;
       // the arc to t first: always admissible (t is at label 0); once it is
       // saturated it takes no part in the relabel
@@ -581,8 +581,8 @@ struct RowSolver {
     }
     int32_t cnt = advance();
     while (cnt > 0) {
-      cl_items += cnt;
-      by_row_width<TPB>(cnt, [&](auto W) { level<decltype(W)::g, false, false>(cnt, 0, wa[2]); });
+      work.cl_items += cnt;
+      by_row_width<TPB>(cnt, [&](auto W) { level<decltype(W)::g, false, false>(cnt, 0, work.arcs[2]); });
       cnt = advance();
       levels++;
     }
@@ -594,13 +594,27 @@ struct RowSolver {
     __syncthreads();
   }
 
-  __device__ __forceinline__ void count_work_done() {
-    count_work(sh, W_SWEEP_ITEMS, wi);
-    count_work(sh, W_SWEEP_ARCS, wa[0]);
-    count_work(sh, W_GR_ITEMS, threadIdx.x == 0 ? gr_items : 0);
-    count_work(sh, W_GR_ARCS, wa[1]);
-    count_work(sh, W_CL_ITEMS, threadIdx.x == 0 ? cl_items : 0);
-    count_work(sh, W_CL_ARCS, wa[2]);
+  // the lanes' counts since the last time into the workgroup's sums
+  __device__ __forceinline__ void count_flush() {
+    const int32_t n[4] = {wave_sum(work.items), wave_sum(work.arcs[0]), wave_sum(work.arcs[1]),
+                          wave_sum(work.arcs[2])};
+    if (lane64() == 0) {
+      atomicAdd(&sh.work[W_SWEEP_ITEMS], (unsigned long long)n[0]);
+      atomicAdd(&sh.work[W_SWEEP_ARCS], (unsigned long long)n[1]);
+      atomicAdd(&sh.work[W_GR_ARCS], (unsigned long long)n[2]);
+      atomicAdd(&sh.work[W_CL_ARCS], (unsigned long long)n[3]);
+    }
+    work.items = work.arcs[0] = work.arcs[1] = work.arcs[2] = 0;
+  }
+  __device__ __forceinline__ void count_step() {
+    if (work.due()) count_flush();
+  }
+  __device__ __forceinline__ void count_end() {
+    count_flush();
+    if (threadIdx.x == 0) {
+      sh.work[W_GR_ITEMS] += (unsigned long long)work.gr_items;
+      sh.work[W_CL_ITEMS] += (unsigned long long)work.cl_items;
+    }
     __syncthreads();
   }
 };
@@ -673,6 +687,7 @@ __device__ __forceinline__ void run_flow(const KArgs &A, Solver &S, SolveShared<
       break;
     }
     cnt = S.pass(cnt, since);
+    S.count_step();
     F.sweeps++;
     if (++since >= rp_eff) relabel = true;
   }
@@ -682,7 +697,7 @@ __device__ __forceinline__ void run_flow(const KArgs &A, Solver &S, SolveShared<
     st.rp_eff = rp_eff;
   }
   if (!F.sliced) S.closure(F.cl_levels);
-  S.count_work_done();
+  S.count_end();
 }
 
 // ---- maximum preflow, smallest source set, balance check, write-back and

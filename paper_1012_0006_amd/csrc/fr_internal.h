@@ -74,6 +74,27 @@ enum {
   W_COUNT
 };
 
+// The row solver's counts within a launch.  The lanes add up 32-bit counts of
+// their own, which go to 64-bit sums every ROW_WORK_STEPS steps (a step: at
+// most one relabel and one pass): a lane takes at most nr G / TPB + 1 rows of
+// 63 arcs per relabel (G = 2) or pass (G = 4), so even with 256 threads and
+// the largest corridor (577,000 vertices) its counts stay below 2^25 and a
+// wave's total below 2^31.
+#define ROW_WORK_STEPS 32
+struct RowWork {
+  int32_t items = 0;              // this lane: vertices with work in passes
+  int32_t arcs[3] = {0, 0, 0};    // arcs touched in passes, relabels, closure
+  int64_t gr_items = 0, cl_items = 0;  // the workgroup: vertices expanded
+  uint32_t steps = 0;
+  // at the end of a step: whether the lanes' counts are to be flushed
+#ifdef __HIPCC__
+  __host__ __device__ __forceinline__
+#endif
+  bool due() {
+    return (++steps & (ROW_WORK_STEPS - 1)) == 0;
+  }
+};
+
 // per-pair sums of the current solve (int64 [P][PA_N]), cleared for the next
 enum {
   PA_CUT = 0,  // pair cut

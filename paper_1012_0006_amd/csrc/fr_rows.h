@@ -98,6 +98,13 @@ __device__ __forceinline__ int32_t group_min(int32_t x) {
   return group_reduce<G>(x, [](int32_t a, int32_t b) { return a < b ? a : b; });
 }
 
+// sum over the wave, the same in every lane
+__device__ __forceinline__ int32_t wave_sum(int32_t x) {
+  const int32_t m = group_sum<16>(x);
+  return __builtin_amdgcn_readlane(m, 0) + __builtin_amdgcn_readlane(m, 16) +
+         __builtin_amdgcn_readlane(m, 32) + __builtin_amdgcn_readlane(m, 48);
+}
+
 // inclusive prefix sum over the group's lanes
 template <int G>
 __device__ __forceinline__ int32_t group_scan(int32_t x) {

@@ -1710,26 +1710,34 @@ extern "C" int32_t fr_mlp_init(fr_context *c, uint64_t seed) {
   return fr_mlp_set_weights(c, w.data(), MLP_NPARAMS);
 }
 
-// Scratch for n samples: x, labels or per-class costs, probs, activations
-// (4*64), backward (5+2*64).
-// Buffers of a network call, carved from one slab that the context keeps and
-// grows on demand (it is given back by fr_destroy).
+// Buffers of a network call, carved from one slab that the context keeps for
+// the next call up to MLP_KEEP bytes (a gradient of about 180,000 samples); a larger
+// one is given back when the call ends.
+#define MLP_KEEP ((size_t)64 << 20)
 struct MlpScratch {
+  DevBufs &d;
   float *x = nullptr, *probs = nullptr, *loss = nullptr, *partial = nullptr;
   double *lossp = nullptr;
   int32_t *labels = nullptr, *idx = nullptr;
   float *xb = nullptr;
   int32_t *lb = nullptr;
   float *costs = nullptr, *cb = nullptr;
+  explicit MlpScratch(fr_context *c) : d(c->d) {}
+  ~MlpScratch() {
+    if (d.mlpcap <= MLP_KEEP) return;
+    dfree(d.mlpbuf);
+    d.mlpbuf = nullptr;
+    d.mlpcap = 0;
+  }
 };
 
 static int64_t mlp_tiles(int64_t n) { return (n + MLP_TILE - 1) / MLP_TILE; }
 
 // n samples; grad_n of them in one gradient (0: forward only); batch rows
 // gathered for training (0: none)
-static int32_t mlp_alloc(fr_context *c, MlpScratch &s, int64_t n, int64_t grad_n, int64_t batch,
+static int32_t mlp_alloc(MlpScratch &s, int64_t n, int64_t grad_n, int64_t batch,
                          bool with_costs = false) {
-  DevBufs &d = c->d;
+  DevBufs &d = s.d;
   for (int pass = 0; pass < 2; pass++) {
     size_t off = 0;
     auto take = [&](auto **ptr, int64_t count) {
@@ -1783,8 +1791,8 @@ static int32_t mlp_gradient(fr_context *c, const float *x, const int32_t *labels
 extern "C" int32_t fr_mlp_forward(fr_context *c, const float *x, int32_t n, float *probs) {
   if (!c || !x || !probs || n < 1 || !c->mlp_loaded) return FR_E_INVALID_ARG;
   HIPCHK(hipSetDevice(c->device));
-  MlpScratch s;
-  int32_t rc = mlp_alloc(c, s, n, 0, 0);
+  MlpScratch s(c);
+  int32_t rc = mlp_alloc(s, n, 0, 0);
   if (rc) return rc;
   HIPCHK(hipMemcpyAsync(s.x, x, sizeof(float) * MLP_IN * n, hipMemcpyHostToDevice, c->cs));
   if ((rc = mlp_forward(c, s.x, n, s))) return rc;
@@ -1796,8 +1804,8 @@ extern "C" int32_t fr_mlp_forward(fr_context *c, const float *x, int32_t n, floa
 extern "C" int32_t fr_mlp_predict(fr_context *c, const float *x, int32_t n, int32_t *alpha) {
   if (!c || !x || !alpha || n < 1 || !c->mlp_loaded) return FR_E_INVALID_ARG;
   HIPCHK(hipSetDevice(c->device));
-  MlpScratch s;
-  int32_t rc = mlp_alloc(c, s, n, 0, 0);
+  MlpScratch s(c);
+  int32_t rc = mlp_alloc(s, n, 0, 0);
   if (rc) return rc;
   HIPCHK(hipMemcpyAsync(s.x, x, sizeof(float) * MLP_IN * n, hipMemcpyHostToDevice, c->cs));
   if ((rc = mlp_forward(c, s.x, n, s))) return rc;
@@ -1838,8 +1846,8 @@ static int32_t mlp_loss_grad(fr_context *c, const float *x, const int32_t *label
   if (!c || !x || n < 1 || !c->mlp_loaded || !mlp_targets_ok(labels, costs, n))
     return FR_E_INVALID_ARG;
   HIPCHK(hipSetDevice(c->device));
-  MlpScratch s;
-  int32_t rc = mlp_alloc(c, s, n, n, 0, costs != nullptr);
+  MlpScratch s(c);
+  int32_t rc = mlp_alloc(s, n, n, 0, costs != nullptr);
   if (rc) return rc;
   HIPCHK(hipMemcpyAsync(s.x, x, sizeof(float) * MLP_IN * n, hipMemcpyHostToDevice, c->cs));
   if (costs)
@@ -1878,8 +1886,8 @@ static int32_t mlp_train(fr_context *c, const float *x, const int32_t *labels, c
   HIPCHK(hipSetDevice(c->device));
   hipStream_t st = c->cs;
   batch = std::min(batch, n);
-  MlpScratch s;
-  int32_t rc = mlp_alloc(c, s, n, batch, batch, costs != nullptr);
+  MlpScratch s(c);
+  int32_t rc = mlp_alloc(s, n, batch, batch, costs != nullptr);
   if (rc) return rc;
   HIPCHK(hipMemcpyAsync(s.x, x, sizeof(float) * MLP_IN * n, hipMemcpyHostToDevice, st));
   if (costs)

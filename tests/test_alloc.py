@@ -229,6 +229,34 @@ assert codes == {0, OOM}, codes
 """)
 
 
+# The network calls keep their buffers, but not those of a call on millions of
+# samples.
+scenario("network_buffers")(r"""
+ctx = context()
+fr.fr_mlp_init(ctx, 1)
+base = hip.fake_used()
+n = 1 << 20
+x, y, cost = np.zeros((n, 8), np.float32), np.zeros(n, np.int32), np.zeros((n, 5), np.float32)
+def calls(n):
+    yield lambda: fr.fr_mlp_forward(ctx, x[:n])
+    yield lambda: fr.fr_mlp_predict(ctx, x[:n])
+    yield lambda: fr.fr_mlp_loss_grad(ctx, x[:n], y[:n])
+    yield lambda: fr.fr_mlp_loss_grad_cost(ctx, x[:n], cost[:n])
+    yield lambda: fr.fr_mlp_train(ctx, x[:n], y[:n], 1, n // 2, 1e-3, 1)
+    yield lambda: fr.fr_mlp_train_cost(ctx, x[:n], cost[:n], 1, n // 2, 1e-3, 1)
+for f in calls(n):
+    f()
+    assert hip.fake_used() - base <= 64 * MB
+for f in calls(16384):
+    f()
+before = hip.fake_mallocs()
+for f in calls(16384):
+    f()
+assert hip.fake_mallocs() == before
+ctx.close()
+""")
+
+
 @pytest.fixture(scope="module")
 def fake_hip(tmp_path_factory):
     if not os.path.exists(fr.LIB_PATH):

@@ -4,6 +4,13 @@
 
 #include "flowrefine.h"
 
+// functions that the host compiler takes too
+#ifdef __HIPCC__
+#define FR_HD __host__ __device__ __forceinline__
+#else
+#define FR_HD inline
+#endif
+
 #define FR_MAX_ALPHA 1024
 #define FR_MAX_ITERS 64
 #define FR_QUEUE 8  // queue words per launch
@@ -87,13 +94,30 @@ struct RowWork {
   int64_t gr_items = 0, cl_items = 0;  // the workgroup: vertices expanded
   uint32_t steps = 0;
   // at the end of a step: whether the lanes' counts are to be flushed
-#ifdef __HIPCC__
-  __host__ __device__ __forceinline__
-#endif
-  bool due() {
-    return (++steps & (ROW_WORK_STEPS - 1)) == 0;
-  }
+  FR_HD bool due() { return (++steps & (ROW_WORK_STEPS - 1)) == 0; }
 };
+
+// KaSPar's stopping rule: p moves since the last best state with gain sum S1
+// and square sum S2 stop the search when p mu^2 > alpha sigma^2 + ln n, i.e.
+// 2^16 (p S1^2 - alpha (p S2 - S1^2)) > beta_fx p^2 with beta_fx = floor(ln n
+// 2^16).
+FR_HD bool mt_stop_int(int64_t p, __int128 S1, __int128 S2, int32_t alpha, int64_t beta_fx) {
+  const __int128 lhs =
+      ((__int128)p * S1 * S1 - (__int128)alpha * ((__int128)p * S2 - S1 * S1)) * 65536;
+  return lhs > (__int128)beta_fx * p * p;
+}
+FR_HD bool mt_stop(int64_t p, __int128 S1, __int128 S2, int32_t alpha, int64_t beta_fx) {
+  if (p < 4096 && S1 > -4096 && S1 < 4096 && S2 < (1 << 24) && alpha < 1024) {
+    // In doubles the same, in a tenth of the instructions: the left side
+    // without its factor is a whole number below 2^47 (p S1^2 < 2^36, alpha p
+    // S2 < 2^46), as are its parts, and the factor 2^16 changes the exponent
+    // only; the right side, with beta_fx < 2^21, is below 2^45.  (The order of
+    // the products matters: alpha * 65536 first would lose the last bits.)
+    const double m = (double)(int32_t)p, s1 = (double)(int32_t)S1, s2 = (double)(int32_t)S2;
+    return (m * s1 * s1 - (double)alpha * (m * s2 - s1 * s1)) * 65536.0 > (double)beta_fx * m * m;
+  }
+  return mt_stop_int(p, S1, S2, alpha, beta_fx);
+}
 
 // per-pair sums of the current solve (int64 [P][PA_N]), cleared for the next
 enum {

@@ -505,23 +505,6 @@ __device__ __forceinline__ void mt_gains(const KArgs &A, MTShared &sh, uint64_t 
   }
 }
 
-// KaSPar's stopping rule: p moves since the last best state with gain sum S1
-// and square sum S2 stop the search when p mu^2 > alpha sigma^2 + ln n, i.e.
-// 2^16 (p S1^2 - alpha (p S2 - S1^2)) > beta_fx p^2 with beta_fx = floor(ln n
-// 2^16).
-__device__ __forceinline__ bool mt_stop(int64_t p, __int128 S1, __int128 S2, int32_t alpha,
-                                        int64_t beta_fx) {
-  if (p < 4096 && S1 > -4096 && S1 < 4096 && S2 < (1 << 24) && alpha < 1024) {
-    // every product is a whole number below 2^53: exact in doubles, and a
-    // tenth of the instructions of the 128-bit form
-    const double m = (double)(int32_t)p, s1 = (double)(int32_t)S1, s2 = (double)(int32_t)S2;
-    return (m * s1 * s1 - (double)alpha * (m * s2 - s1 * s1)) * 65536.0 > (double)beta_fx * m * m;
-  }
-  const __int128 lhs =
-      ((__int128)p * S1 * S1 - (__int128)alpha * ((__int128)p * S2 - S1 * S1)) * 65536;
-  return lhs > (__int128)beta_fx * p * p;
-}
-
 // The multi-try rounds of all pairs of the round, in pair order (one
 // workgroup: the first wave searches, the others compute gains at its
 // request).

@@ -708,7 +708,6 @@ template <int TPB, bool ROWS>
 __device__ __forceinline__ void flow_pair(const KArgs &A, int32_t p, SolveShared<TPB> &sh,
                                           PairState &st, const int32_t *lc = nullptr) {
   const PairView V = make_view(A, p);
-  const int32_t a = V.a, b = V.b;
   int64_t *pa = A.pacc + (int64_t)p * PA_N;
   if (threadIdx.x == 0) {
     st = A.ps[p];

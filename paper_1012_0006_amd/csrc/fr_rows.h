@@ -25,6 +25,10 @@
 // The form takes networks with edge weights up to 32,767, at most 63 arcs per
 // vertex, and rows that fit the entry's arc slice; the others keep the CSR
 // form (Arc records of any weight and degree).  Both give the same results.
+// Measured on a round of 8 pairs (2D, 2^20 vertices, mean degree 8): 43 ms
+// with rows in all entries but one hub's, 113 ms with every entry in the CSR
+// form, where what k_net_count writes of the rows before it finds the misfit
+// is lost, and 125 ms in that form before there were rows.
 #pragma once  // included by fr_kernels.h, after its wave and list helpers
 
 typedef unsigned long long u64;

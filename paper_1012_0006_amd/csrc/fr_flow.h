@@ -725,10 +725,17 @@ __device__ __forceinline__ void flow_pair(const KArgs &A, int32_t p, SolveShared
   const int32_t nr = uni(st.nr);
   int64_t t0 = wall_clock64();
   const int32_t NL = nr + 2;
-  const bool overflow = pa[PA_RCAP] >= 0x7fffffffLL;
+  // networks that can't be solved: too large capacities (net_rev reports
+  // them), and rows with an arc whose reverse is missing
+  const bool torn = ROWS && pa[PA_REV] != 0;
+  const bool unsolvable = pa[PA_RCAP] >= 0x7fffffffLL || torn;
+  if (torn && threadIdx.x == 0) {
+    A.ctl->err = FR_E_INVALID_GRAPH;
+    A.ctl->diag = DIAG_REV;
+  }
   Rot R;
   FlowStats F;
-  if (!overflow) {
+  if (!unsolvable) {
     if constexpr (ROWS) {
       // labels in LDS when they fit beside the bitmaps and lists
       if (nr <= ROW_LABEL_MAX && row_lds_bytes(nr) + row_label_bytes(nr) <= A.flow_lds) {
@@ -771,13 +778,13 @@ __device__ __forceinline__ void flow_pair(const KArgs &A, int32_t p, SolveShared
   // largest minimum source side (label >= NL: cannot reach the sink)
   int64_t acc[7] = {0, 0, 0, 0, 0, 0, 0};
   const bool term = A.terminals != 0;
-  const bool mb = A.mb_reps > 0 && !overflow;
-  const int side_mode = (A.mb_reps > 0 || overflow) ? 0 : A.cut_side;
+  const bool mb = A.mb_reps > 0 && !unsolvable;
+  const int side_mode = (A.mb_reps > 0 || unsolvable) ? 0 : A.cut_side;
   if (mb) {
     if (threadIdx.x == 0) sh.nfree = 0;
     __syncthreads();
   }
-  if (!overflow) {
+  if (!unsolvable) {
     BLOCK_WAVE_LOOP(i, nr) {
       bool fv = false;
       if (i < nr) {

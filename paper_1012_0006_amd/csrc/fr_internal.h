@@ -131,6 +131,7 @@ enum {
   PA_RCIN,     // weight of the old a-b edges the solve decides
   PA_CS,       // contracted terminals: capacity out of s (the initial excess)
   PA_MISFIT,   // corridor vertices that do not fit the row form
+  PA_REV,      // row form: finished words minus arcs (0: every arc has its reverse)
   PA_N
 };
 

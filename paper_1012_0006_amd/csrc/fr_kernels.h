@@ -302,9 +302,12 @@ __global__ void __launch_bounds__(256) k_graph_stats(KArgs A, int64_t narcs) {
   int64_t sum = 0;
   int32_t mx = 0, md = 0, mw = 0;
   int bad = 0;
+  // (a negative weight, which only unchecked input can have, fits no row)
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < narcs;
-       e += (int64_t)gridDim.x * blockDim.x)
-    mw = max(mw, A.adjwgt[e]);
+       e += (int64_t)gridDim.x * blockDim.x) {
+    const int32_t w = A.adjwgt[e];
+    mw = max(mw, w < 0 ? 0x7fffffff : w);
+  }
   for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u < A.n;
        u += (int64_t)gridDim.x * blockDim.x) {
     const int32_t w = A.vwgt[u];
@@ -1812,8 +1815,8 @@ __device__ __forceinline__ void net_count(const KArgs &A, Items &&items) {
         if (xv[q] != a && xv[q] != b) continue;
         if (c + q >= e1) continue;
         if (mv[q] == S) {
-          if (w[q] > ROW_MAX_W) fit = false;
-          if (fit) (cnt < ROW_SLOTS ? own : more)[cnt] = row_word(w[q], w[q], lv[q], 0);
+          if ((uint32_t)w[q] > ROW_MAX_W) fit = false;
+          if (fit) (cnt < ROW_SLOTS ? own : more)[cnt] = row_word(w[q], w[q], lv[q], ROW_RAW);
           cnt++;
           cap += w[q];
           if (!side && xv[q] == b) cin += w[q];
@@ -1953,8 +1956,12 @@ __global__ void __launch_bounds__(256) k_net_fill(KArgs A, int32_t it) {
 //
 // Row form: the lower end of each edge finds the arc's slot in the other row
 // and finishes both words (reverse slots, and the saturation when one end is
-// a source-border vertex; the excess then goes to the other end).
-__device__ __forceinline__ void net_rev_row(const KArgs &A, int32_t p, int32_t i, bool src,
+// a source-border vertex; the excess then goes to the other end).  Returns
+// what the vertex adds to PA_REV: the words it finished minus its arcs.  Only
+// unfinished words are taken, so a sum of 0 means that every word is finished.
+// An arc without its reverse (input that was not checked) makes it less, and
+// the solve is left out: the row of its head has no word to push through.
+__device__ __forceinline__ int32_t net_rev_row(const KArgs &A, int32_t p, int32_t i, bool src,
                                             bool saturate) {
   u64 *L = rows_of(A, p);
   const int32_t nr = A.ps[p].nr;
@@ -1962,12 +1969,14 @@ __device__ __forceinline__ void net_rev_row(const KArgs &A, int32_t p, int32_t i
   const uint8_t *fl = A.lflag + vb;
   const u64 head = L[(int64_t)ROW_WORDS * i];
   const int32_t deg = (int32_t)(head >> 32), ovf = (int32_t)(uint32_t)head;
+  const uint32_t want = ((uint32_t)ROW_RAW << 26) | (uint32_t)i;  // an unfinished word with head i
+  int32_t finished = 0;
   for (int32_t s = 0; s < deg; s++) {
     const int64_t at = s < ROW_SLOTS ? (int64_t)ROW_WORDS * i + 1 + s
                                      : (int64_t)ROW_WORDS * (nr + ovf) + (s - ROW_SLOTS);
     const u64 x = L[at];
     const int32_t h = row_head(x);
-    if (h < i) continue;
+    if (h < i || (h == i && row_rslot(x) != ROW_RAW)) continue;
     // its slot in h's row: the own row first, eight 16-byte loads together
     const u64x2 *R = reinterpret_cast<const u64x2 *>(L + (int64_t)ROW_WORDS * h);
     u64 y[ROW_WORDS];
@@ -1981,11 +1990,11 @@ __device__ __forceinline__ void net_rev_row(const KArgs &A, int32_t p, int32_t i
     int32_t t = -1;
 #pragma unroll
     for (int q = 1; q < ROW_WORDS; q++)
-      if (q <= dh && row_head(y[q]) == i) t = q - 1;
+      if (q <= dh && (uint32_t)(y[q] >> 32) == want) t = q - 1;
     if (t < 0) {
       const u64 *more = L + (int64_t)ROW_WORDS * (nr + (int32_t)(uint32_t)y[0]) - ROW_SLOTS;
       for (int32_t q = ROW_SLOTS; q < dh; q++)
-        if (row_head(more[q]) == i) {
+        if ((uint32_t)(more[q] >> 32) == want) {
           t = q;
           break;
         }
@@ -2005,11 +2014,17 @@ __device__ __forceinline__ void net_rev_row(const KArgs &A, int32_t p, int32_t i
     }
     L[at] = row_word(own, rv, h, t);
     L[row_index(L, nr, h, t)] = row_word(rv, own, i, s);
+    finished += h == i && t == s ? 1 : 2;
   }
+  return finished - deg;
 }
 
 template <typename Items>
 __device__ __forceinline__ void net_rev(const KArgs &A, Items &&items) {
+  KeyedSums<1> sums;
+  auto out = [&](int, int key, int64_t v) {
+    wave_add_by_key((unsigned long long *)A.pacc, PA_N, PA_REV, key, v);
+  };
   items([&](int32_t p, int64_t item64) {
     const bool on = p >= 0;
     const int32_t item = (int32_t)item64;
@@ -2027,7 +2042,9 @@ __device__ __forceinline__ void net_rev(const KArgs &A, Items &&items) {
     const bool src = on && LF_SRC(f);
     const bool snk = on && LF_SNK(f);
     const bool rows = on && rows_chosen(A, p);
-    if (rows) net_rev_row(A, p, item, src, !A.terminals && !overflow);
+    int64_t off[1] = {0};
+    if (rows) off[0] = net_rev_row(A, p, item, src, !A.terminals && !overflow);
+    sums.add(rows ? p : -1, off, out);
     const int32_t b0 = on && !rows ? lo[item] : 0, e0 = on && !rows ? lo[item + 1] : 0;
     int64_t ex = 0;
     for (int32_t ar = b0; ar < e0; ar++) {
@@ -2067,6 +2084,7 @@ __device__ __forceinline__ void net_rev(const KArgs &A, Items &&items) {
     const int pos = wave_append_by_key(A.pcnt + A.P, snk ? p : -1);
     if (snk) put_bounded(A.SNK + vb, pos, A.voff[p + 1] - vb, item, A.ctl);
   });
+  sums.flush(out);
 }
 
 __global__ void __launch_bounds__(256) k_net_rev(KArgs A, int32_t it) {

@@ -38,6 +38,7 @@ typedef __attribute__((ext_vector_type(2))) unsigned long long u64x2;
 #define ROW_SLOTS 15       // arcs in a vertex's own row
 #define ROW_MAX_DEG 63     // slots fit 6 bits
 #define ROW_MAX_W 32767    // own + reverse residual fit 16 bits each
+#define ROW_RAW 63         // slot of a word whose reverse arc has not been found yet
 
 __device__ __forceinline__ int32_t row_own(u64 x) { return (int32_t)((uint32_t)x & 0xffffu); }
 __device__ __forceinline__ int32_t row_rev(u64 x) { return (int32_t)((uint32_t)x >> 16); }
